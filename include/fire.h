@@ -161,9 +161,9 @@ int fire_init(fire_ctx **out, const fire_mesh *mesh, const fire_fuel *cats, int3
  * flux_sens / flux_lat (device atmosphere arrays) and updates the state in
  * the arena.  If out is not NULL it receives device pointers to the new
  * psi, t_i and F (valid until the next fire_step) and the new time.  Enqueues
- * the fused step kernel and, while an ignition is active (Sect. 4.4), a small
- * kernel before it that forms the step's ignition geometry and per-tile
- * set-up in the arena.
+ * the fused step kernel and, for the tiled kernel while an ignition is active
+ * (Sect. 4.4), a small kernel before it that forms the step's ignition
+ * geometry and per-tile set-up in the arena.
  *
  * Boundary policy 0 (Sect. 4.1: the run terminates when fire reaches the
  * guard ring): after each step the status word is copied to pinned host
@@ -209,7 +209,9 @@ int fire_coef(fire_ctx *ctx, double *out, int32_t ncat);
 int fire_ros_eval(fire_ctx *ctx, const uint8_t *cat, const void *un, const void *tn, void *S,
                   int64_t n);
 
-/* Tile shape of the fused step kernel: tile_x a multiple of sr_x with
+/* Tile shape of the tiled step kernel, which the context takes from then on
+ * (a context whose shape was never set takes the kernel and the work-group
+ * shape that its mesh is fastest with): tile_x a multiple of sr_x with
  * tile_x <= 122, tile_y a multiple of sr_y with tile_y <= 42 (FP32) or
  * <= 26 (FP64).  Results do not depend on the tile shape.  The arena holds
  * the per-tile ignition set-up for as many tiles as the default shape has;
@@ -296,8 +298,8 @@ int fire_ens_get_state(fire_ens *e, fire_view *out);
 /* Sticky FIRE_STATUS_* bits of every member into host status[ndom] (waits). */
 int fire_ens_status(fire_ens *e, int32_t *status);
 
-/* Tile shape (same limits as fire_set_tile()); rebuilds the tile work list
- * (waits).  Not to be called during graph capture. */
+/* Tile shape (meaning and limits as for fire_set_tile()); rebuilds the tile
+ * work list (waits).  Not to be called during graph capture. */
 int fire_ens_set_tile(fire_ens *e, int32_t tile_x, int32_t tile_y);
 int fire_ens_get_tile(fire_ens *e, int32_t *tile_x, int32_t *tile_y);
 
@@ -313,8 +315,9 @@ size_t fire_ens_tune_bytes(fire_ens *e);
 
 /*
  * Times reps steps for each candidate tile shape cand[2*i], cand[2*i+1]
- * (i < ncand) with the given inputs, keeps the fastest (written to best[2])
- * and restores the state, time and status from a snapshot in the caller's
+ * (i < ncand) and for the kernel an ensemble without a set shape takes, with
+ * the given inputs, keeps the fastest (the fastest candidate is written to
+ * best[2]) and restores the state, time and status from a snapshot in the caller's
  * scratch (fire_ens_tune_bytes(), 256-byte aligned), so the ensemble is left
  * as before the call except for the tile shape.  The flux buffers are
  * overwritten.  Waits.

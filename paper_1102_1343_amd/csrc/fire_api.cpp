@@ -83,6 +83,45 @@ void ignition_window(const fire_ignition *ign, int n, double *lo, double *hi) {
     }
 }
 
+// Which step kernel a mesh (or an ensemble of ncells cells in all) takes when
+// no tile shape was chosen, and the shape of a work-group's tile.
+//
+// Small tiles (fire_small.hip) where the mesh is too small to fill the GPU
+// with the 120 x 20 tiles of fire_kernels.hip: the step is then the latency of
+// one work-group, not throughput.  Measured, us per step small / tiled: 128^2
+// FP32 7.6 / 17, FP64 9.3 / 35; 300^2 8.6 / 17, 14 / 35; 600^2 14.6 / 17.8,
+// 32 / 36; 700^2 15.7-22.6 / 18-20, 39 / 39; 800^2 18-24 / 18-20, 47 / 47;
+// 1000^2 25 / 21, 65 / 51 (the rings computed twice and the waves' number
+// cost more than the latency saves): the line is at 400 000 cells.
+// The tile is the smallest of whole atmosphere cells, at least 8 cells a
+// side, that gives at most 700 work-groups (256 CUs, two or three each).
+StepKind step_kind(const fire_mesh *m, int ndom, int *tx, int *ty) {
+    int64_t cells = 0;
+    for (int k = 0; k < ndom; k++) cells += (int64_t)m[k].nx * m[k].ny;
+    const int sx = m->sr_x, sy = m->sr_y;
+    // nodes of a tile with its two inner rings: two per thread, and LDS of at
+    // most 64 KiB with 256 fuels
+    const int most = m->dtype == FIRE_F64 ? 1024 : 2048;
+    if (cells <= kSmallCells) {
+        int x = (8 + sx - 1) / sx * sx, y = (8 + sy - 1) / sy * sy;
+        for (;;) {
+            int64_t n = 0;
+            for (int k = 0; k < ndom; k++)
+                n += (int64_t)((m[k].nx + x - 1) / x) * ((m[k].ny + y - 1) / y);
+            const int x1 = x < y ? x + sx : x, y1 = x < y ? y : y + sy;
+            if (n <= 700 || (x1 + 4) * (y1 + 4) > most) break;
+            x = x1;
+            y = y1;
+        }
+        if ((x + 4) * (y + 4) <= most) {
+            *tx = x;
+            *ty = y;
+            return kSmall;
+        }
+    }
+    return kTiled;
+}
+
 bool tile_ok(const fire_mesh *m, int tile_x, int tile_y) {
     const int ymax = m->dtype == FIRE_F64 ? kTileYMax64 : kTileYMax;
     if (tile_x < 1 || tile_x > kTileXMax || tile_x % m->sr_x != 0) return false;
@@ -156,8 +195,9 @@ hipError_t step_raw(fire_ctx *c, const void *psi_in, void *psi_out, void *tign, 
     a.ny = m.ny;
     a.tile_x = c->tile_x;
     a.tile_y = c->tile_y;
-    a.tiles_x = (m.nx + c->tile_x - 1) / c->tile_x;
-    const int tiles_y = (m.ny + c->tile_y - 1) / c->tile_y;
+    const StepKind kind = c->tile_set ? kTiled : step_kind(&m, 1, &a.tile_x, &a.tile_y);
+    a.tiles_x = (m.nx + a.tile_x - 1) / a.tile_x;
+    const int tiles_y = (m.ny + a.tile_y - 1) / a.tile_y;
     a.ntiles = a.tiles_x * tiles_y;
     a.per_xcd = (a.ntiles + 7) / 8;
     a.sr_x = m.sr_x;
@@ -209,7 +249,9 @@ hipError_t step_raw(fire_ctx *c, const void *psi_in, void *psi_out, void *tign, 
     a.ign_rows = m.ny + kFHMax;
     b.ign_set = state_ptr(c, c->off_iset);
 
-    return launch_step(m.dtype, a, b, stream ? stream : c->stream);
+    if (!stream) stream = c->stream;
+    if (kind == kSmall) return launch_step_small(m.dtype, a, b, c->ign, stream);
+    return launch_step(m.dtype, a, b, stream);
 }
 
 }  // namespace fire
@@ -282,6 +324,7 @@ int fire_init(fire_ctx **out, const fire_mesh *mesh, const fire_fuel *cats, int3
     c->mark = nullptr;
     c->mark_step = 0;
     c->nstep = 0;
+    c->tile_set = 0;
     default_tile(mesh, &c->tile_x, &c->tile_y);
     if (!tile_ok(mesh, c->tile_x, c->tile_y)) {
         delete c;
@@ -483,6 +526,7 @@ int fire_set_tile(fire_ctx *c, int32_t tile_x, int32_t tile_y) {
     if (!c || !tile_ok(&c->mesh, tile_x, tile_y)) return FIRE_ERR_ARG;
     c->tile_x = tile_x;
     c->tile_y = tile_y;
+    c->tile_set = 1;
     return FIRE_OK;
 }
 

@@ -26,6 +26,10 @@ template <> struct M<float> {
     static __device__ __forceinline__ float div(float a, float b) {
         return a * __builtin_amdgcn_rcpf(b);
     }
+    // 1 - a / b
+    static __device__ __forceinline__ float one_m_div(float a, float b) {
+        return __builtin_fmaf(-a, __builtin_amdgcn_rcpf(b), 1.0f);
+    }
     // 1 - exp(-x); its absolute rounding error is that of F itself
     static __device__ __forceinline__ float one_m_exp_neg(float x) {
         return 1.0f - __builtin_amdgcn_exp2f(-1.4426950408889634f * x);
@@ -38,6 +42,7 @@ template <> struct M<double> {
     static __device__ __forceinline__ double rsqrt(double x) { return 1.0 / ::sqrt(x); }
     static __device__ __forceinline__ double sqrt(double x) { return ::sqrt(x); }
     static __device__ __forceinline__ double div(double a, double b) { return a / b; }
+    static __device__ __forceinline__ double one_m_div(double a, double b) { return 1.0 - a / b; }
     static __device__ __forceinline__ double one_m_exp_neg(double x) { return -::expm1(-x); }
     static __device__ __forceinline__ double inf() { return __builtin_huge_val(); }
 };
@@ -58,6 +63,12 @@ __device__ __forceinline__ float med3(float x, float lo, float hi) {
 __device__ __forceinline__ double med3(double x, double lo, double hi) {
     return vmin(vmax(x, lo), hi);
 }
+
+// Fused multiply-add as one rounding, whatever the compiler's contraction
+// setting: the ignition geometry below is evaluated by the step kernels and
+// by the reverse kernels, which must take exactly the forward's values.
+__device__ __forceinline__ float fmaT(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fmaT(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 // Spread rate, Eq. (3), with the category multiplier and the cap:
 // S = min{cap, m max{S0, R0 + c min{e, max{0,U}}^b + d max{0, tan phi}^2}}.
@@ -112,7 +123,7 @@ template <typename T>
 __device__ __forceinline__ T ros_v4(const V4<T> &r0, const V4<T> &r1, T un, T tn, T cap) {
     const T U = med3(un, T(0), r1.x);
     const T g = vmax(tn, T(0));
-    const T s = r0.x + r0.y * M<T>::powp(U, r0.w) + r0.z * (g * g);
+    const T s = fmaT(r0.z, g * g, fmaT(r0.y, M<T>::powp(U, r0.w), r0.x));
     return med3(s, r1.y, cap);
 }
 template <typename T>
@@ -130,6 +141,28 @@ __device__ __forceinline__ T ros_row(const lds_t<T> *row, T un, T tn, T cap) {
     return ros_v4(r0, r1, un, tn, cap);
 }
 
+// A table row's spread-rate entries in registers.
+template <typename T> struct RosRow {
+    V4<T> r0;       // R0 c d b
+    T e, floor;
+};
+template <typename T> __device__ __forceinline__ RosRow<T> read_row(const lds_t<T> *row) {
+    const lds_t<V4<T>> *q = reinterpret_cast<const lds_t<V4<T>> *>(row);
+    RosRow<T> r;
+    r.r0.x = q[0].x; r.r0.y = q[0].y; r.r0.z = q[0].z; r.r0.w = q[0].w;
+    r.e = q[1].x;
+    r.floor = q[1].y;
+    return r;
+}
+template <typename T>
+__device__ __forceinline__ T ros_row(const RosRow<T> &row, T un, T tn, T cap) {
+    V4<T> r1;
+    r1.x = row.e;
+    r1.y = row.floor;
+    r1.z = r1.w = T(0);
+    return ros_v4(row.r0, r1, un, tn, cap);
+}
+
 // Right-hand side of Eq. (12) at a node from its value pc and its four
 // neighbours (west, east, south, north).  The Godunov choice of Eq. (13)
 // enters only through its square, which for every sign pattern is
@@ -138,36 +171,120 @@ __device__ __forceinline__ T ros_row(const lds_t<T> *row, T un, T tn, T cap) {
 // factor 1/2 cancels in the normal) straight from the two nodes, so it is
 // exactly zero when they are equal -- as at a domain corner whose ghosts
 // mirror the inner nodes -- whatever the compiler fuses.
+// Every product that is fused with a sum is written as a fused multiply-add
+// and contraction is off, so each kernel that calls this (the tiled step, the
+// streamed step, the replays) gets the same bits.
 template <typename T, typename RowPtr>
 __device__ __forceinline__ T rhs5(T pc, T pw, T pe, T ps, T pn, T u, T v, T gzx, T gzy,
                                   RowPtr row, const Consts<T> &c) {
-    const T dmx = (pc - pw) * c.rdx, dpx = (pe - pc) * c.rdx;
-    const T dmy = (pc - ps) * c.rdy, dpy = (pn - pc) * c.rdy;
+#pragma clang fp contract(off)
+    const T de = pe - pc, dn = pn - pc;
+    const T dmx = (pc - pw) * c.rdx, dpx = de * c.rdx;
+    const T dmy = (pc - ps) * c.rdy, dpy = dn * c.rdy;
     // max(max(D-,0)^2, min(D+,0)^2) = max(D-, -D+, 0)^2 exactly
     const T gx = vmax(vmax(dmx, -dpx), T(0)), gy = vmax(vmax(dmy, -dpy), T(0));
-    const T up = M<T>::sqrt(gx * gx + gy * gy);
+    const T up = M<T>::sqrt(fmaT(gx, gx, gy * gy));
     const T cx = (pe - pw) * c.rdx, cy = (pn - ps) * c.rdy;
-    const T cn2 = cx * cx + cy * cy;
+    const T cn2 = fmaT(cx, cx, cy * cy);
     const T inv = cn2 > T(0) ? M<T>::rsqrt(cn2) : T(0);
     const T nx = cx * inv, ny = cy * inv;
-    const T S = ros_row(row, u * nx + v * ny, gzx * nx + gzy * ny, c.cap);
-    const T lap = (dpx - dmx) + (dpy - dmy);
-    const T visc = c.visc_mode == 0 ? c.eps * S * lap : c.eps * lap;
-    return visc - S * up;
+    const T S = ros_row(row, fmaT(u, nx, v * ny), fmaT(gzx, nx, gzy * ny), c.cap);
+    const T lap = fmaT(de, c.rdx, -dmx) + fmaT(dn, c.rdy, -dmy);
+    const T kl = c.visc_mode == 0 ? c.eps * S : c.eps;
+    return fmaT(lap, kl, -(up * S));
 }
 
-// Fused multiply-add as one rounding, whatever the compiler's contraction
-// setting: the ignition geometry below is evaluated by the step kernels and
-// by the reverse kernels, which must take exactly the forward's values.
-__device__ __forceinline__ float fmaT(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fmaT(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// The two stages of Eq. (11) at a node: psi* = psi' + dt F, and
+// psi^{n+1} = (psi' + psi*)/2 + dt/2 F*.
+template <typename T> __device__ __forceinline__ T heun1(T p, T dt, T f) { return fmaT(dt, f, p); }
+template <typename T> __device__ __forceinline__ T heun2(T p, T b, T hdt, T f) {
+#pragma clang fp contract(off)
+    return fmaT(T(0.5), p + b, hdt * f);
+}
+
+// Ignition time of a node crossed in the step from time t (Eq. 14).
+__device__ __forceinline__ float cross_time(float t, float p, float pn, float dt) {
+#pragma clang fp contract(off)
+    return fmaT(p * dt, __builtin_amdgcn_rcpf(p - pn), t);
+}
+__device__ __forceinline__ double cross_time(double t, double p, double pn, double dt) {
+#pragma clang fp contract(off)
+    return t + (p * dt) / (p - pn);
+}
+
+// Fuel fraction of one cell at t' (Eqs. 15-19) from the 3x3 node values of
+// psi^{n+1} (p[b][a], b the row from the south, a the column) and of the node
+// ignition times t^ (q, already t' where psi >= 0).  Four sub-cells with
+// corners at the centre, two edge midpoints and a cell corner, bilinear
+// values, t^ reset to t' where psi >= 0 there.
+template <typename T>
+__device__ __forceinline__ T fraction9(const T (&p)[3][3], const T (&q)[3][3], T tp, T rTf) {
+#pragma clang fp contract(off)
+    // edge midpoints and corners shared by neighbouring sub-cells
+    const T pc = p[1][1], qc = q[1][1];
+    T pmax = p[0][0];
+#pragma unroll
+    for (int b = 0; b < 3; b++)
+#pragma unroll
+        for (int a = 0; a < 3; a++) pmax = vmax(pmax, p[b][a]);
+    // every node burning: every sub-cell corner value is a mean of negative
+    // values, so beta = 1 exactly in all four sub-cells (Eq. 18) and t^ is
+    // t_i at every corner.  A wave whose lanes are all such cells takes the
+    // short sums, any other the general ones for all lanes (the same values:
+    // one path per wave is cheaper than both)
+    const bool all_burning = pmax < T(0);
+    const bool brief = __builtin_amdgcn_ballot_w64(!all_burning) == 0;
+    T pe[2][2], qe[2][2];   // [0][s]: x edges (s = left/right), [1][s]: y edges
+#pragma unroll
+    for (int s = 0; s < 2; s++) {
+        pe[0][s] = T(0.5) * (pc + p[1][2 * s]);
+        qe[0][s] = T(0.5) * (qc + q[1][2 * s]);
+        pe[1][s] = T(0.5) * (pc + p[2 * s][1]);
+        qe[1][s] = T(0.5) * (qc + q[2 * s][1]);
+    }
+    T burned = T(0);
+    if (brief) {
+#pragma unroll
+        for (int sb = 0; sb < 2; sb++)
+#pragma unroll
+            for (int sa = 0; sa < 2; sa++) {
+                const T qk[4] = {qc, qe[0][sa], qe[1][sb],
+                                 T(0.25) * (qc + q[1][2 * sa] + q[2 * sb][1] + q[2 * sb][2 * sa])};
+                T tau = T(0);
+#pragma unroll
+                for (int k = 0; k < 4; k++) tau += tp - qk[k];
+                burned += M<T>::one_m_exp_neg(T(0.25) * tau * rTf);
+            }
+    } else {
+#pragma unroll
+        for (int sb = 0; sb < 2; sb++)
+#pragma unroll
+            for (int sa = 0; sa < 2; sa++) {
+                const T pk[4] = {pc, pe[0][sa], pe[1][sb],
+                                 T(0.25) * (pc + p[1][2 * sa] + p[2 * sb][1] + p[2 * sb][2 * sa])};
+                const T qk[4] = {qc, qe[0][sa], qe[1][sb],
+                                 T(0.25) * (qc + q[1][2 * sa] + q[2 * sb][1] + q[2 * sb][2 * sa])};
+                T sum = T(0), asum = T(0), tau = T(0);
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    sum += pk[k];
+                    asum += vabs(pk[k]);
+                    tau += pk[k] >= T(0) ? T(0) : (tp - qk[k]);
+                }
+                T beta = asum > T(0) ? T(0.5) * M<T>::one_m_div(sum, asum) : T(0);
+                beta = all_burning ? T(1) : beta;
+                burned += beta * M<T>::one_m_exp_neg(T(0.25) * tau * rTf);
+            }
+    }
+    return T(1) - T(0.25) * burned;
+}
 
 // One ignition's geometry at time t (IgnGeo): plain IEEE operations with no
 // contraction into fused multiply-adds, so every kernel that forms it (the
 // per-step table of the step kernels, the reverse kernels) gets the same
 // bits.
 template <typename T>
-__device__ __forceinline__ bool ign_setup(const fire_ignition &g, double t, IgnGeo<T> &o) {
+__host__ __device__ __forceinline__ bool ign_setup(const fire_ignition &g, double t, IgnGeo<T> &o) {
 #pragma clang fp contract(off)
     const bool torch = (g.vx != 0.0 || g.vy != 0.0);
     const double tend = torch ? g.t_end : g.t_start;
@@ -211,6 +328,27 @@ __device__ __forceinline__ T ign_py(const IgnGeo<T> &g, int gy, double dy) {
 }
 template <typename T> __device__ __forceinline__ T ign_by(const IgnGeo<T> &g, T py) {
     return py * g.eyL;
+}
+
+// Bounds of psi_g (Eq. 21) over the nodes of a frame of fw columns and fh
+// rows whose first node is global (fx0, fy0): the distance from the frame's
+// centre to the segment -/+ the frame's half diagonal, less the radius,
+// widened by a margin (1 m + 1e-4 of the distances) far above the rounding of
+// psi_g and of the bounds themselves.  Node (i, j) sits at ((i + 1/2) dx,
+// (j + 1/2) dy), so the centre is (fx0 + fw/2, fy0 + fh/2) cells.
+template <typename T>
+__device__ __forceinline__ void ign_frame_bounds(const IgnGeo<T> &gs, int fx0, int fy0, int fw,
+                                                 int fh, double dx, double dy, T &lb, T &ub) {
+    const T cx = T((fx0 + 0.5 * fw) * dx - gs.ax);
+    const T cy = T((fy0 + 0.5 * fh) * dy - gs.ay);
+    const T hx = T(0.5 * (fw - 1)) * T(dx), hy = T(0.5 * (fh - 1)) * T(dy);
+    const T hd = M<T>::sqrt(hx * hx + hy * hy);
+    const T sp = med3(cx * gs.exL + cy * gs.eyL, T(0), T(1));
+    const T qx = cx - sp * gs.ex, qy = cy - sp * gs.ey;
+    const T d = M<T>::sqrt(qx * qx + qy * qy);
+    const T mg = T(1) + T(1e-4) * (d + M<T>::sqrt(gs.ex * gs.ex + gs.ey * gs.ey));
+    lb = d - hd - gs.rad - mg;
+    ub = d + hd - gs.rad + mg;
 }
 
 // Nearest point of the segment (Eq. 20): parameter s in [0, 1], the offset

@@ -27,6 +27,9 @@ struct fire_ens {
     const void *dzdx, *dzdy;
     hipStream_t stream;
     int tile_x, tile_y, ntiles;
+    int tile_set;   // the tile shape was chosen by fire_ens_set_tile
+    StepKind kind;  // the step kernel of the current work list and its tile
+    int unit_x, unit_y;
     int schedule;   // FIRE_ENS_GRID or FIRE_ENS_RESIDENT
     int slots;      // resident work-groups of the current tile shape
 };
@@ -95,10 +98,15 @@ size_t layout(fire_ens *e) {
 
 char *ptr(fire_ens *e, size_t off) { return e->arena + off; }
 
-// Domain table and tile -> domain work list for the current tile shape and
-// schedule: members in index order on the grid schedule, largest first on
+// The step kernel, domain table and tile -> domain work list for the current
+// tile shape and schedule: members in index order on the grid schedule, largest first on
 // the resident one (so the bands end with small members' tiles).
 int build_worklist(fire_ens *e) {
+    e->unit_x = e->tile_x;
+    e->unit_y = e->tile_y;
+    e->kind = kTiled;
+    if (!e->tile_set && e->schedule == FIRE_ENS_GRID)
+        e->kind = step_kind(e->meshes.data(), e->ndom, &e->unit_x, &e->unit_y);
     std::vector<EnsDomain> doms(e->ndom);
     std::vector<int32_t> map;
     map.reserve(e->map_cap);
@@ -116,8 +124,8 @@ int build_worklist(fire_ens *e) {
         std::memset(&d, 0, sizeof(d));
         d.nx = m.nx;
         d.ny = m.ny;
-        d.tiles_x = (m.nx + e->tile_x - 1) / e->tile_x;
-        const int tiles_y = (m.ny + e->tile_y - 1) / e->tile_y;
+        d.tiles_x = (m.nx + e->unit_x - 1) / e->unit_x;
+        const int tiles_y = (m.ny + e->unit_y - 1) / e->unit_y;
         d.tile0 = tile0;
         d.nax = (m.nx + m.sr_x - 1) / m.sr_x;
         d.nay = (m.ny + m.sr_y - 1) / m.sr_y;
@@ -209,6 +217,7 @@ int fire_ens_init(fire_ens **out, const fire_mesh *meshes, int32_t ndom, const f
     e->dzdy = dzdy;
     e->stream = (hipStream_t)stream;
     e->schedule = FIRE_ENS_GRID;
+    e->tile_set = 0;
     default_tile(&meshes[0], &e->tile_x, &e->tile_y);
     if (!tile_ok(&meshes[0], e->tile_x, e->tile_y)) {
         delete e;
@@ -265,8 +274,8 @@ int fire_ens_step(fire_ens *e, const void *u, const void *v, double dt, void *fl
     if (!(dt > 0.0) || !std::isfinite(dt)) return FIRE_ERR_ARG;
     StepArgs a;
     std::memset(&a, 0, sizeof(a));
-    a.tile_x = e->tile_x;
-    a.tile_y = e->tile_y;
+    a.tile_x = e->unit_x;
+    a.tile_y = e->unit_y;
     a.ntiles = e->ntiles;
     a.per_xcd = (e->ntiles + 7) / 8;
     a.sr_x = e->sr_x;
@@ -301,7 +310,13 @@ int fire_ens_step(fire_ens *e, const void *u, const void *v, double dt, void *fl
     b.ens_doms = (const EnsDomain *)ptr(e, e->off_dom);
     b.ens_tile_dom = (const int32_t *)ptr(e, e->off_map);
     b.ens_clock = (const EnsClock *)ptr(e, e->off_t);
-    hipError_t h = launch_step(e->dtype, a, b, e->stream);
+    hipError_t h;
+    if (e->kind == kSmall) {
+        h = launch_ens_geo(e->dtype, a, b, e->stream);
+        if (h == hipSuccess) h = launch_step_small(e->dtype, a, b, nullptr, e->stream);
+    } else {
+        h = launch_step(e->dtype, a, b, e->stream);
+    }
     if (h == hipSuccess) h = launch_advance_clock((EnsClock *)ptr(e, e->off_t), dt, e->stream);
     return h == hipSuccess ? FIRE_OK : FIRE_ERR_HIP;
 }
@@ -339,6 +354,7 @@ int fire_ens_set_tile(fire_ens *e, int32_t tile_x, int32_t tile_y) {
     if (!e || !tile_ok(&e->meshes[0], tile_x, tile_y)) return FIRE_ERR_ARG;
     e->tile_x = tile_x;
     e->tile_y = tile_y;
+    e->tile_set = 1;
     return build_worklist(e);
 }
 
@@ -408,8 +424,17 @@ int fire_ens_autotune(fire_ens *e, const void *u, const void *v, double dt, void
     }
     float best_ms = 0.0f;
     int best_i = -1, rc = FIRE_OK;
-    for (int i = 0; i < ncand && rc == FIRE_OK; i++) {
-        rc = fire_ens_set_tile(e, cand[2 * i], cand[2 * i + 1]);
+    // the candidates, then (i == ncand) the kernel that is taken when no
+    // shape is set, where that is another one
+    bool own_best = false;
+    for (int i = 0; i <= ncand && rc == FIRE_OK; i++) {
+        if (i < ncand) {
+            rc = fire_ens_set_tile(e, cand[2 * i], cand[2 * i + 1]);
+        } else {
+            e->tile_set = 0;
+            rc = build_worklist(e);
+            if (rc == FIRE_OK && e->kind == kTiled) break;
+        }
         if (rc != FIRE_OK) break;
         rc = fire_ens_step(e, u, v, dt, flux_sens, flux_lat);   // warm-up
         if (rc != FIRE_OK) break;
@@ -422,7 +447,8 @@ int fire_ens_autotune(fire_ens *e, const void *u, const void *v, double dt, void
         if (rc == FIRE_OK && hipEventElapsedTime(&ms, ev0, ev1) != hipSuccess) rc = FIRE_ERR_HIP;
         if (rc == FIRE_OK && (best_i < 0 || ms < best_ms)) {
             best_ms = ms;
-            best_i = i;
+            if (i < ncand) best_i = i;
+            else own_best = true;
         }
         // restore the snapshot into the buffer that is current again
         h = copy(ptr(e, e->off_psi[cur0]), sc + o_psi, n);
@@ -438,6 +464,10 @@ int fire_ens_autotune(fire_ens *e, const void *u, const void *v, double dt, void
     best[0] = cand[2 * best_i];
     best[1] = cand[2 * best_i + 1];
     rc = fire_ens_set_tile(e, best[0], best[1]);
+    if (rc == FIRE_OK && own_best) {
+        e->tile_set = 0;
+        rc = build_worklist(e);
+    }
     if (rc == FIRE_OK && hipStreamSynchronize(e->stream) != hipSuccess) rc = FIRE_ERR_HIP;
     return rc;
 }

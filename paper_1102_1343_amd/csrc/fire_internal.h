@@ -158,6 +158,7 @@ struct fire_ctx {
     double t;              // model time of the current state
     hipStream_t stream;
     int tile_x, tile_y;
+    int tile_set;          // the tile shape was chosen by fire_set_tile
     int stopped;           // FIRE_ERR_BOUNDARY / FIRE_ERR_NONFINITE once the stop
                            // policy has seen that status bit, else 0
     // Stop policy: after each step the status word is copied to pinned host
@@ -177,6 +178,11 @@ namespace fire {
 
 // launchers (return hipError_t of the launch)
 hipError_t launch_step(int dtype, const StepArgs &a, const StepBuffers &b, hipStream_t s);
+// the step with a small tile per work-group (fire_small.hip): one domain or an
+// ensemble; its threads per work-group and nodes per thread
+void small_block(int tile_x, int tile_y, int *npt, int *nt);
+hipError_t launch_step_small(int dtype, const StepArgs &a, const StepBuffers &b,
+                             const fire_ignition *ign, hipStream_t s);
 hipError_t launch_coef(int dtype, const fire_fuel *fuels_dev, int ncat, double wind_cap,
                        void *coef_dev, hipStream_t s);
 hipError_t launch_fill(int dtype, void *psi, void *tign, void *frac, size_t n, double psi0,
@@ -185,6 +191,8 @@ hipError_t launch_ros_eval(int dtype, const void *coef, int ncat, double ros_cap
                            const uint8_t *cat, const void *un, const void *tn, void *S,
                            int64_t n, hipStream_t s);
 hipError_t launch_coef_to_f64(int dtype, const void *coef, double *out, int n, hipStream_t s);
+// the ignition geometry of an ensemble step (launch_step does it itself)
+hipError_t launch_ens_geo(int dtype, const StepArgs &a, const StepBuffers &b, hipStream_t s);
 hipError_t launch_advance_clock(EnsClock *c, double dt, hipStream_t s);
 // resident work-groups of the ensemble step for this tile height (0: query failed)
 int persist_slots(int dtype, int tile_y, int ncat, size_t ncells);
@@ -199,6 +207,10 @@ bool fuels_ok(const fire_fuel *cats, int ncat);
 bool ignitions_ok(const fire_ignition *ign, int nign);
 void default_tile(const fire_mesh *m, int *tx, int *ty);
 bool tile_ok(const fire_mesh *m, int tile_x, int tile_y);
+// the step kernels, and the one for these meshes when no tile shape was chosen
+enum StepKind { kTiled, kSmall };
+constexpr int64_t kSmallCells = 400000;   // cells in all that take the small tiles
+StepKind step_kind(const fire_mesh *m, int ndom, int *tx, int *ty);
 // [lo, hi] outside which none of the ignitions is active (the activity test
 // of the step kernel, in the same double arithmetic); lo > hi when n = 0.
 void ignition_window(const fire_ignition *ign, int n, double *lo, double *hi);

@@ -128,31 +128,8 @@ template <typename T> __device__ __forceinline__ T wave_reduce_max(T m) {
                 vmax(lane_value(m, 32), lane_value(m, 48)));
 }
 
-// Bounds of psi_g (Eq. 21) over the nodes of a frame of kFW columns and fh
-// rows whose first node is global (fx0, fy0): the distance from the frame's
-// centre to the segment -/+ the frame's half diagonal, less the radius,
-// widened by a margin (1 m + 1e-4 of the distances) far above the rounding of
-// psi_g and of the bounds themselves.  Node (i, j) sits at ((i + 1/2) dx,
-// (j + 1/2) dy), so the centre is (fx0 + kFW/2, fy0 + fh/2) cells.
-template <typename T>
-__device__ __forceinline__ void ign_frame_bounds(const IgnGeo<T> &gs, int fx0, int fy0, int fh,
-                                                 double dx, double dy, T &lb, T &ub) {
-    const T cx = T((fx0 + 0.5 * kFW) * dx - gs.ax);
-    const T cy = T((fy0 + 0.5 * fh) * dy - gs.ay);
-    const T hx = T(0.5 * (kFW - 1)) * T(dx), hy = T(0.5 * (fh - 1)) * T(dy);
-    const T hd = M<T>::sqrt(hx * hx + hy * hy);
-    const T sp = med3(cx * gs.exL + cy * gs.eyL, T(0), T(1));
-    const T qx = cx - sp * gs.ex, qy = cy - sp * gs.ey;
-    const T d = M<T>::sqrt(qx * qx + qy * qy);
-    const T mg = T(1) + T(1e-4) * (d + M<T>::sqrt(gs.ex * gs.ex + gs.ey * gs.ey));
-    lb = d - hd - gs.rad - mg;
-    ub = d + hd - gs.rad + mg;
-}
-
-// Fuel fraction of one cell at t' (Eqs. 15-19) from the 3x3 node values of
-// psi^{n+1} (A) and of the node ignition times t^ (Q, already t' where
-// psi >= 0).  Four sub-cells with corners at the centre, two edge midpoints
-// and a cell corner, bilinear values, t^ reset to t' where psi >= 0 there.
+// Fuel fraction of the cell at frame position (fy, fx) of psi^{n+1} (A) and of
+// the node ignition times (Q).
 template <typename T>
 __device__ __forceinline__ T cell_fraction(const T (*A)[kFW], int fy, const T (*Q)[kFW], int qy,
                                            int fx, T tp, T rTf) {
@@ -164,52 +141,7 @@ __device__ __forceinline__ T cell_fraction(const T (*A)[kFW], int fy, const T (*
             p[b][a] = A[fy + b - 1][fx + a - 1];
             q[b][a] = Q[qy + b - 1][fx + a - 1];
         }
-    // edge midpoints and corners shared by neighbouring sub-cells
-    const T pc = p[1][1], qc = q[1][1];
-    T pmax = p[0][0];
-#pragma unroll
-    for (int b = 0; b < 3; b++)
-#pragma unroll
-        for (int a = 0; a < 3; a++) pmax = vmax(pmax, p[b][a]);
-    // every node burning: every sub-cell corner value is a mean of negative
-    // values, so beta = 1 exactly in all four sub-cells (Eq. 18) and t^ is
-    // t_i at every corner; the sums keep the general path's order
-    const bool all_burning = pmax < T(0);
-    T pe[2][2], qe[2][2];   // [0][s]: x edges (s = left/right), [1][s]: y edges
-#pragma unroll
-    for (int s = 0; s < 2; s++) {
-        pe[0][s] = T(0.5) * (pc + p[1][2 * s]);
-        qe[0][s] = T(0.5) * (qc + q[1][2 * s]);
-        pe[1][s] = T(0.5) * (pc + p[2 * s][1]);
-        qe[1][s] = T(0.5) * (qc + q[2 * s][1]);
-    }
-    T burned = T(0);
-#pragma unroll
-    for (int sb = 0; sb < 2; sb++)
-#pragma unroll
-        for (int sa = 0; sa < 2; sa++) {
-            const T pk[4] = {pc, pe[0][sa], pe[1][sb],
-                             T(0.25) * (pc + p[1][2 * sa] + p[2 * sb][1] + p[2 * sb][2 * sa])};
-            const T qk[4] = {qc, qe[0][sa], qe[1][sb],
-                             T(0.25) * (qc + q[1][2 * sa] + q[2 * sb][1] + q[2 * sb][2 * sa])};
-            if (all_burning) {
-                T tau = T(0);
-#pragma unroll
-                for (int k = 0; k < 4; k++) tau += tp - qk[k];
-                burned += M<T>::one_m_exp_neg(T(0.25) * tau * rTf);
-                continue;
-            }
-            T sum = T(0), asum = T(0), tau = T(0);
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                sum += pk[k];
-                asum += vabs(pk[k]);
-                tau += pk[k] >= T(0) ? T(0) : (tp - qk[k]);
-            }
-            const T beta = asum > T(0) ? T(0.5) * (T(1) - M<T>::div(sum, asum)) : T(0);
-            burned += beta * M<T>::one_m_exp_neg(T(0.25) * tau * rTf);
-        }
-    return T(1) - T(0.25) * burned;
+    return fraction9(p, q, tp, rTf);
 }
 
 // The fused step.  KR = frame rows per thread (frame height <= 4 KR).
@@ -361,7 +293,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int ty, const u
             geo_on[tid] = on ? 1 : 0;
             geo_s[tid] = gs;
             if (on)
-                ign_frame_bounds(gs, x0 - kHalo, y0 - kHalo, FHM, a.dx, a.dy, geo_lb[tid],
+                ign_frame_bounds(gs, x0 - kHalo, y0 - kHalo, kFW, FHM, a.dx, a.dy, geo_lb[tid],
                                  geo_ub[tid]);
         }
         // the frame's largest psi^n (NaN nodes, which no ignition changes,
@@ -463,7 +395,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int ty, const u
         if (in1(k)) {
             const lds_t<T> *row = tab3 + __umul24(min((uint32_t)cur.cv, ncm1), (uint32_t)kLRow);
             const T F1 = rhs(A, fy, tx, cur.u, cur.v, cur.gx, cur.gy, row, c);
-            B[fy - 1][tx] = p0[k] + dt * F1;
+            B[fy - 1][tx] = heun1(p0[k], dt, F1);
         }
     }
     __syncthreads();
@@ -501,7 +433,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int ty, const u
             const lds_t<T> *row = tab3 + __umul24(min((uint32_t)cur.cv, ncm1), (uint32_t)kLRow);
             const T F2 = rhs(B, fy - 1, tx, cur.u, cur.v, cur.gx, cur.gy, row, c);
             const T pn0 = A[fy][tx];
-            const T pn = T(0.5) * (pn0 + B[fy - 1][tx]) + hdt * F2;
+            const T pn = heun2(pn0, B[fy - 1][tx], hdt, F2);
             A[fy][tx] = pn;   // stage-1 reads of A ended at the last barrier
             // t_i is read only where it can matter: a burning node, a node
             // crossing zero, or a node lit by this step's ignition
@@ -511,7 +443,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int ty, const u
                 ti = told;
                 if (is_inf(ti)) ti = tig[k];
                 if (pn0 > T(0) && pn <= T(0) && is_inf(ti))
-                    ti = t + M<T>::div(pn0 * dt, pn0 - pn);
+                    ti = cross_time(t, pn0, pn, dt);
             }
             if (!REC) C[fy - 2][tx] = pn >= T(0) ? tp : ti;
             if (xr3 && fy >= 3 && fy < a.tile_y + 3) {
@@ -870,7 +802,7 @@ k_ign_plain(const fire_ignition *__restrict__ ign, int nign, double t, const Ste
         const int fx0 = txi * a.tile_x - kHalo, fy0 = tyi * a.tile_y - kHalo;
         T lb[FIRE_MAX_IGNITIONS], ub[FIRE_MAX_IGNITIONS];
         for (int g = 0; g < nign; g++)
-            if (on[g]) ign_frame_bounds(geo[g], fx0, fy0, fhm, a.dx, a.dy, lb[g], ub[g]);
+            if (on[g]) ign_frame_bounds(geo[g], fx0, fy0, kFW, fhm, a.dx, a.dy, lb[g], ub[g]);
         uint32_t word = 0;
         for (int g = 0; g < nign; g++) {
             if (!on[g]) continue;
@@ -999,6 +931,15 @@ template <typename T> __global__ void k_to_f64(const T *src, double *dst, int n)
     if (i < n) dst[i] = (double)src[i];
 }
 
+// An ensemble step's ignition geometry, ahead of its step kernel.
+template <typename T> hipError_t ens_geo(const StepArgs &a, const StepBuffers &b, hipStream_t s) {
+    const int nth = b.ndom * FIRE_MAX_IGNITIONS;
+    hipLaunchKernelGGL((k_ign_geo<T>), dim3((nth + 63) / 64), dim3(64), 0, s, b.ign, a.nign, a.t,
+                       b.ens_doms, b.ens_clock, b.ndom, (char *)b.ign_tab,
+                       b.ens_slots > 0 ? b.ens_counters : nullptr);
+    return hipGetLastError();
+}
+
 template <typename T, int KR, bool SMALL>
 hipError_t launch_one(const StepArgs &a, const StepBuffers &b, hipStream_t s) {
     const size_t dyn = (size_t)a.ncat * kLRow * sizeof(T);
@@ -1018,10 +959,8 @@ hipError_t launch_one(const StepArgs &a, const StepBuffers &b, hipStream_t s) {
                            a.nign, a.t, a, kNR * KR, (IgnTable<T> *)b.ign_tab,
                            (uint32_t *)iuse, (T *)ilb, (T *)irow);
     } else if (b.ens_doms) {
-        const int nth = b.ndom * FIRE_MAX_IGNITIONS;
-        hipLaunchKernelGGL((k_ign_geo<T>), dim3((nth + 63) / 64), dim3(64), 0, s, b.ign,
-                           a.nign, a.t, b.ens_doms, b.ens_clock, b.ens_doms ? b.ndom : 1,
-                           (char *)b.ign_tab, b.ens_slots > 0 ? b.ens_counters : nullptr);
+        const hipError_t h = ens_geo<T>(a, b, s);
+        if (h != hipSuccess) return h;
     }
     if (b.ens_doms && b.ens_slots > 0) {
         hipLaunchKernelGGL((k_ens_persist<T, KR, SMALL>), dim3(b.ens_slots), dim3(kFW, kNR), dyn,
@@ -1122,6 +1061,10 @@ int persist_slots(int dtype, int tile_y, int ncat, size_t ncells) {
 
 hipError_t launch_step(int dtype, const StepArgs &a, const StepBuffers &b, hipStream_t s) {
     return dtype == FIRE_F64 ? step_t<double>(a, b, s) : step_t<float>(a, b, s);
+}
+
+hipError_t launch_ens_geo(int dtype, const StepArgs &a, const StepBuffers &b, hipStream_t s) {
+    return dtype == FIRE_F64 ? ens_geo<double>(a, b, s) : ens_geo<float>(a, b, s);
 }
 
 hipError_t launch_advance_clock(EnsClock *c, double dt, hipStream_t s) {
