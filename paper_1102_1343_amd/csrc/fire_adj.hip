@@ -257,11 +257,10 @@ __device__ __forceinline__ double block_sum_rt(double v, double *sh) {
     return r;
 }
 
-// shift_reduce over the kRT threads of a reversed-step block.
+// shift_reduce over the kRT threads of a reversed-step block, where some
+// thread has a contribution.
 __device__ __forceinline__ void shift_reduce_rt(int g, double cx, double cy, int nign,
                                                 double *acc, double *sh, int b) {
-    const int any = __syncthreads_or(g >= 0);
-    if (!any) return;
     for (int k = 0; k < nign; k++) {
         const double sx = block_sum_rt(g == k ? cx : 0.0, sh);
         const double sy = block_sum_rt(g == k ? cy : 0.0, sh);
@@ -402,22 +401,15 @@ __device__ __forceinline__ T node_g(const AdjArgs &a, const T *P, int x, int y) 
     return P[y * nx + x];
 }
 
-// Sum of the stage partials (planes c, w, e, s, n of D) aimed at interior
-// node (x, y), plus its share of the side ghosts extrapolated from it.  A
-// cell whose adjoint weight W is zero wrote no partials (they are zero), so
-// they are read only where W != 0.
+// A node's share of the side ghosts extrapolated from it, added to the sum s
+// of the stage partials (planes c, w, e, s, n of D) aimed at it.  A cell whose
+// adjoint weight W is zero wrote no partials (they are zero), so they count
+// only where W != 0.
 template <typename T>
-__device__ __forceinline__ T gather_node(const AdjArgs &a, const T *D, const T *W, const T *P,
-                                         int x, int y) {
+__device__ __forceinline__ T gather_ghosts(const AdjArgs &a, const T *D, const T *W, const T *P,
+                                           int x, int y, T s) {
     const int nx = a.nx, ny = a.ny;
     const size_t n = (size_t)nx * ny;
-    const int i = y * nx + x;
-    T s = T(0);
-    if (W[i] != T(0)) s += D[i];
-    if (x + 1 < nx && W[i + 1] != T(0)) s += D[n + i + 1];
-    if (x - 1 >= 0 && W[i - 1] != T(0)) s += D[2 * n + i - 1];
-    if (y + 1 < ny && W[i + nx] != T(0)) s += D[3 * n + i + nx];
-    if (y - 1 >= 0 && W[i - nx] != T(0)) s += D[4 * n + i - nx];
     T dp, dq;
     if (x <= 1 && W[y * nx] != T(0)) {
         dghost(P[y * nx], P[y * nx + 1], dp, dq);
@@ -464,6 +456,62 @@ __device__ __forceinline__ void stage_D(const RhsGrad<T> &r, int i, size_t n, T 
     D[4 * n + i] = q * r.dn;
 }
 
+// The five stencil values at node (x, y) of a level set, loaded
+// unconditionally (neighbours outside the domain read the node itself) and the
+// side ghosts formed from them: they are extrapolated from the node and its
+// opposite neighbour.
+template <typename T> struct Five {
+    T c, w, e, s, n;
+};
+template <typename T>
+__device__ __forceinline__ Five<T> load5(const AdjArgs &a, const T *P, int i, int x, int y) {
+    const int nx = a.nx;
+    Five<T> v;
+    v.c = P[i];
+    v.w = P[x > 0 ? i - 1 : i];
+    v.e = P[x < nx - 1 ? i + 1 : i];
+    v.s = P[y > 0 ? i - nx : i];
+    v.n = P[y < a.ny - 1 ? i + nx : i];
+    return v;
+}
+template <typename T>
+__device__ __forceinline__ Five<T> with_ghosts(const AdjArgs &a, const Five<T> &v, int x, int y) {
+    Five<T> r = v;
+    if (x == 0) r.w = ghost(v.c, v.e);
+    if (x == a.nx - 1) r.e = ghost(v.c, v.w);
+    if (y == 0) r.s = ghost(v.c, v.n);
+    if (y == a.ny - 1) r.n = ghost(v.c, v.s);
+    return r;
+}
+
+// Leading columns of the coefficient table that the derivatives read (S0 to
+// m), copied to LDS.
+constexpr int kRevCoef = kM + 1;
+
+// What a stage derivative reads at a node besides the level set.
+template <typename T> struct NodeIn {
+    T u, v, gzx, gzy;
+    int cat;
+};
+
+// Derivatives of stage F at a node from its stencil values; coefs: the LDS
+// copy of the coefficients.  The table row is formed in registers, as
+// stage_grad does, so that both round alike.
+template <typename T>
+__device__ __forceinline__ RhsGrad<T> stage_grad5(const AdjArgs &a, const Five<T> &p, int x, int y,
+                                                  const NodeIn<T> &in, const T *coefs) {
+    const Five<T> q = with_ghosts(a, p, x, y);
+    const int cv = in.cat < a.ncat - 1 ? in.cat : a.ncat - 1;
+    T g[kNCoef];
+#pragma unroll
+    for (int j = 0; j < kRevCoef; j++) g[j] = coefs[cv * kRevCoef + j];
+    g[kTf] = T(1);
+    g[kCh] = g[kCq] = T(0);
+    alignas(16) T row[kLRow];
+    make_row(g, row, T(a.cap));
+    return rhs5_grad(q.c, q.w, q.e, q.s, q.n, in.u, in.v, in.gzx, in.gzy, row, g, consts<T>(a));
+}
+
 // Ignition state of node (x, y) at the start of a step: psi' = min over the
 // active ignitions (the last one lowering it is `sel`), and the ignition
 // whose arrival time a node lit in this step takes (`tsel`).
@@ -487,8 +535,55 @@ __device__ __forceinline__ void ignite_node(const AdjArgs &a, const fire_ignitio
 
 // Reverse, part 1 at node i for step n: the ignition time set in the step
 // (Eq. 14 for a crossing node, the arrival time for a node lit by an
-// ignition) passes dL/dt_i on; then the stage-2 partials weighted by
-// dt/2 dL/dpsi^{n+1}.  Returns dL/dpsi^{n+1} with the crossing part added.
+// ignition) passes dL/dt_i on.  set: the step set the node's time; lt: dL/dt_i
+// (cleared where it is passed on); p, q: psi' and psi^{n+1}.  Returns
+// dL/dpsi^{n+1} with the crossing part added; lp0: that of dL/dpsi'.
+template <typename T>
+__device__ __forceinline__ T rev1_time(const AdjArgs &a, bool set, int x, int y, T lam, T psi_n,
+                                       T p, T q, T &lt_, T &lp0, const fire_ignition *ign, int &g,
+                                       double &cx, double &cy) {
+    lp0 = T(0);
+    if (!set) return lam;
+    const T lt = lt_;
+    lt_ = T(0);
+    if (p > T(0)) {
+        const T D2 = (p - q) * (p - q);
+        const T dt = T(a.dt);
+        const T iD2 = M<T>::div(T(1), D2);
+        lam += lt * dt * p * iD2;
+        lp0 = -lt * dt * q * iD2;
+    } else if (lt != T(0)) {
+        int sg, k;
+        ignite_node(a, ign, psi_n, x, y, sg, k);
+        IgnGeo<T> geo;
+        if (k >= 0 && ign_setup<T>(ign[k], a.t, geo)) {
+            const T px = ign_px(geo, x, a.dx);
+            const T py = ign_py(geo, y, a.dy);
+            const IgnNear<T> nq = ign_near(geo, px, py, ign_by(geo, py));
+            const bool sfree = nq.s > T(0) && nq.s < T(1);
+            const T d = M<T>::sqrt(nq.d2);
+            const T arr = fmaT(d, geo.invS, fmaT(nq.s, geo.lenv, geo.tg));
+            if (arr < geo.t) {
+                // translating the ignition by delta moves the node by -delta
+                T ax_ = T(0), ay_ = T(0);
+                if (d > T(0)) {
+                    ax_ = -geo.invS * M<T>::div(nq.qx, d);
+                    ay_ = -geo.invS * M<T>::div(nq.qy, d);
+                }
+                if (sfree) {
+                    ax_ -= geo.lenv * geo.exL;
+                    ay_ -= geo.lenv * geo.eyL;
+                }
+                g = k;
+                cx = (double)(lt * ax_);
+                cy = (double)(lt * ay_);
+            }
+        }
+    }
+    return lam;
+}
+
+// Part 1 at node i with its stage-2 partials (weight dt/2 dL/dpsi^{n+1}).
 template <typename T>
 __device__ __forceinline__ T rev1_node(const AdjArgs &a, int n, int i, int x, int y, T lam,
                                        const int32_t *set_step, const T *psi_n, const T *P0,
@@ -499,43 +594,9 @@ __device__ __forceinline__ T rev1_node(const AdjArgs &a, int n, int i, int x, in
                                        double &cy) {
     T lp0 = T(0);
     if (set_step[i] == n) {
-        const T lt = LT[i];
-        LT[i] = T(0);
-        const T p = P0[i], q = pn1[i];
-        if (p > T(0)) {
-            const T D2 = (p - q) * (p - q);
-            const T dt = T(a.dt);
-            const T iD2 = M<T>::div(T(1), D2);
-            lam += lt * dt * p * iD2;
-            lp0 = -lt * dt * q * iD2;
-        } else if (lt != T(0)) {
-            int sg, k;
-            ignite_node(a, ign, psi_n[i], x, y, sg, k);
-            IgnGeo<T> geo;
-            if (k >= 0 && ign_setup<T>(ign[k], a.t, geo)) {
-                const T px = ign_px(geo, x, a.dx);
-                const T py = ign_py(geo, y, a.dy);
-                const IgnNear<T> nq = ign_near(geo, px, py, ign_by(geo, py));
-                const bool sfree = nq.s > T(0) && nq.s < T(1);
-                const T d = M<T>::sqrt(nq.d2);
-                const T arr = fmaT(d, geo.invS, fmaT(nq.s, geo.lenv, geo.tg));
-                if (arr < geo.t) {
-                    // translating the ignition by delta moves the node by -delta
-                    T ax_ = T(0), ay_ = T(0);
-                    if (d > T(0)) {
-                        ax_ = -geo.invS * M<T>::div(nq.qx, d);
-                        ay_ = -geo.invS * M<T>::div(nq.qy, d);
-                    }
-                    if (sfree) {
-                        ax_ -= geo.lenv * geo.exL;
-                        ay_ -= geo.lenv * geo.eyL;
-                    }
-                    g = k;
-                    cx = (double)(lt * ax_);
-                    cy = (double)(lt * ay_);
-                }
-            }
-        }
+        T lt = LT[i];
+        lam = rev1_time(a, true, x, y, lam, psi_n[i], P0[i], pn1[i], lt, lp0, ign, g, cx, cy);
+        LT[i] = lt;
     }
     LP0[i] = lp0;
     if (lam != T(0))
@@ -547,7 +608,7 @@ __device__ __forceinline__ T rev1_node(const AdjArgs &a, int n, int i, int x, in
 // Sum of the stage-1 partials aimed at owned node (x, y), from the tile's
 // LDS copy of dL/dpsi* (W) and of the partial planes (Dc, Dw, De, Ds, Dn) on
 // the tile and its ring, plus its share of the side ghosts extrapolated from
-// it: gather_node in the same order of terms.  (ex, ey) is the node's
+// it, in the order of the stage-2 gather.  (ex, ey) is the node's
 // position in the ringed tile; P (psi') comes from memory for the ghost
 // formula.
 template <typename T>
@@ -584,21 +645,21 @@ __device__ __forceinline__ T gather_lds(const AdjArgs &a, const T (*W)[kREX],
     return s;
 }
 
-// Reverse, part 3 at owned node i for step n, given the gathered stage-1
+// Reverse, part 3 at an owned node for step n, given the gathered stage-1
 // partials (gath) and dL/dpsi* (lb): dL/dpsi' = gathered partials + crossing part +
 // dL/dpsi^{n+1}/2 + dL/dpsi*, then through the ignition minimum: returns
 // dL/dpsi^n (zero where an ignition set psi', whose shift gets the
 // contribution instead).
 template <typename T>
-__device__ __forceinline__ T rev3_lds(const AdjArgs &a, int i, int x, int y, T l1, T lb, T gath,
-                                      const T *LP0, const T *psi_n, const fire_ignition *ign,
-                                      int &g, double &cx, double &cy) {
+__device__ __forceinline__ T rev3_lds(const AdjArgs &a, int x, int y, T l1, T lb, T gath, T lp0,
+                                      T psi_n, const fire_ignition *ign, int &g, double &cx,
+                                      double &cy) {
     T l = gath;
-    l += LP0[i];
+    l += lp0;
     l += T(0.5) * l1;
     l += lb;
     int sg = -1, tg;
-    if (a.ign_active) ignite_node(a, ign, psi_n[i], x, y, sg, tg);
+    if (a.ign_active) ignite_node(a, ign, psi_n, x, y, sg, tg);
     if (sg < 0) return l;
     IgnGeo<T> geo;
     if (l != T(0) && ign_setup<T>(ign[sg], a.t, geo)) {
@@ -679,6 +740,14 @@ k_rev_part1(const AdjArgs a, int n, const int32_t *set_step, const T *psi_n, con
 // L1i and the stage-2 partials from Di; writes dL/dpsi^n (part 1 of step
 // n - 1 applied) to L1o and that step's stage-2 partials to Do: the ring
 // reads its neighbours' inputs, so those two are double-buffered.
+//
+// Bound by latency: at most a few hundred tiles are live, one work-group each,
+// and a step of the chain is a launch.  So a thread owns one node of the
+// ringed tile through all parts and loads all it may read there at once, after
+// one round trip for the flags (each wave takes its own vote of them); the
+// fuel table comes through LDS, so no load waits for another.  1024^2
+// FP32, 100 steps: 22 -> 14 us per reversed step (several tiles per
+// work-group, to spare the dead ones' launch: 15.7, live tiles then queue).
 template <typename T>
 __global__ void __launch_bounds__(kRT)
 k_rev_tile(const AdjArgs a2, const AdjArgs a1, int part1, int n1, const T *Di, const T *L1i,
@@ -688,53 +757,109 @@ k_rev_tile(const AdjArgs a2, const AdjArgs a1, int part1, int n1, const T *Di, c
            const uint8_t *cat, const T *coef, const fire_ignition *ign, double *gu, double *gv,
            double *gm, double *acc, AdjFlags fl) {
     __shared__ T W[kREY][kREX];          // dL/dpsi* on the tile and its ring
-    __shared__ T Dp[5][kREY][kREX];      // its stage-1 partials (c, w, e, s, n)
-    __shared__ double sh[kRT];
+    // its stage-1 partials (c, w, e, s, n); then the shift sums' scratch
+    __shared__ __attribute__((aligned(8))) T Dp[5][kREY][kREX];
+    static_assert(sizeof(Dp) >= kRT * sizeof(double), "scratch of the shift sums");
+    double *sh = reinterpret_cast<double *>(&Dp[0][0][0]);
+    __shared__ int votes;
+    extern __shared__ __attribute__((aligned(32))) double dyn_smem[];
+    T *coefs = reinterpret_cast<T *>(dyn_smem);
     const AdjArgs &a = a2;
     const int nx = a.nx, ny = a.ny;
+    const int ntx = rtiles_x(a), nty = rtiles_y(a);
+    const int e = threadIdx.x, lane = e & 63;
     const int t = blockIdx.x;
-    const int x0 = (t % rtiles_x(a)) * kRTX, y0 = (t / rtiles_x(a)) * kRTY;
-    const bool live = nbhd_flag(f_l1i, a, t) || fl.lp0[t] || (part1 && fl.lt[t]);
-    if (!live) {
+    const int cy_ = t / ntx, cx_ = t - cy_ * ntx;
+    const int x0 = cx_ * kRTX, y0 = cy_ * kRTY;
+    // the flags within reach: lanes 0-8 of each wave take the tile and its
+    // neighbours, 9 and 10 the tile's other two
+    int f = 0;
+    {
+        const int fx = cx_ + lane % 3 - 1, fy = cy_ + lane / 3 - 1;
+        if (lane < 9 && fx >= 0 && fx < ntx && fy >= 0 && fy < nty) f = f_l1i[fy * ntx + fx];
+        if (lane == 9) f = fl.lp0[t];
+        if (lane == 10 && part1) f = fl.lt[t];
+    }
+    if (__builtin_amdgcn_ballot_w64(f != 0) == 0) {
         // every output is zero: clear what the output buffer holds from two
         // steps ago
         if (f_l1o[t]) {
-            const int q = threadIdx.x;
-            const int x = x0 + q % kRTX, y = y0 + q / kRTX;
-            if (q < kRTX * kRTY && x < nx && y < ny) L1o[y * nx + x] = T(0);
-            if (threadIdx.x == 0) f_l1o[t] = 0;
+            const int x = x0 + e % kRTX, y = y0 + e / kRTX;
+            if (e < kRTX * kRTY && x < nx && y < ny) L1o[y * nx + x] = T(0);
+            __syncthreads();   // every wave has read the flag
+            if (e == 0) f_l1o[t] = 0;
         }
         return;
     }
-    // ---- part 2 on the tile and its ring, one node per thread
-    const int e = threadIdx.x;
-    const int ex2 = e % kREX, ey2 = e / kREX;
-    const int x2 = x0 - 1 + ex2, y2 = y0 - 1 + ey2;
-    if (e < kREX * kREY && x2 >= 0 && x2 < nx && y2 >= 0 && y2 < ny) {
-        const int ex = ex2, ey = ey2, x = x2, y = y2;
-        const int i = y * nx + x;
-        const T l1 = L1i[i];
-        T lb = gather_node(a, Di, L1i, B, x, y);
+    for (int k = e; k < a.ncat * kRevCoef; k += kRT)
+        coefs[k] = coef[k / kRevCoef * kNCoef + k % kRevCoef];
+    // ---- one node of the tile and its ring per thread: all its loads
+    const int ex = e % kREX, ey = e / kREX;
+    const int x = x0 - 1 + ex, y = y0 - 1 + ey;
+    const bool in = e < kREX * kREY && x >= 0 && x < nx && y >= 0 && y < ny;
+    const bool own = in && ex >= 1 && ex <= kRTX && ey >= 1 && ey <= kRTY;
+    const int i = in ? y * nx + x : 0;
+    const size_t n = (size_t)nx * ny;
+    Five<T> l5 = {}, d5 = {}, b5 = {}, p5 = {}, q5 = {};
+    NodeIn<T> nin = {};
+    double du = 0.0, dv = 0.0, dm = 0.0;
+    T lp0 = T(0), ps = T(0), lt = T(0), ps1 = T(0), p01 = T(0);
+    int32_t ss = -1;
+    if (in) {
+        l5 = load5(a, L1i, i, x, y);
+        d5.c = Di[i];
+        d5.e = Di[n + (x < nx - 1 ? i + 1 : i)];        // the east cell's west partial
+        d5.w = Di[2 * n + (x > 0 ? i - 1 : i)];
+        d5.n = Di[3 * n + (y < ny - 1 ? i + nx : i)];
+        d5.s = Di[4 * n + (y > 0 ? i - nx : i)];
+        b5 = load5(a, B, i, x, y);
+        p5 = load5(a, P0, i, x, y);
+        nin.u = u[i];
+        nin.v = v[i];
+        nin.gzx = gzx[i];
+        nin.gzy = gzy[i];
+        nin.cat = cat[i];
+    }
+    if (own) {
+        du = gu[i];
+        dv = gv[i];
+        dm = gm[i];
+        lp0 = LP0[i];
+        ps = psi_n[i];
+        lt = LT[i];
+        if (part1) {
+            ss = set_step[i];
+            ps1 = psi_n1[i];
+            p01 = P0n1[i];
+            q5 = load5(a, Bn1, i, x, y);
+        }
+    }
+    if (e == 0) votes = 0;
+    __syncthreads();
+
+    // ---- part 2
+    if (in) {
+        const T l1 = l5.c;
+        T lb = T(0);
+        if (l1 != T(0)) lb += d5.c;
+        if (x + 1 < nx && l5.e != T(0)) lb += d5.e;
+        if (x - 1 >= 0 && l5.w != T(0)) lb += d5.w;
+        if (y + 1 < ny && l5.n != T(0)) lb += d5.n;
+        if (y - 1 >= 0 && l5.s != T(0)) lb += d5.s;
+        lb = gather_ghosts(a, Di, L1i, B, x, y, lb);
         lb += T(0.5) * l1;
         W[ey][ex] = lb;
-        const bool own = ex >= 1 && ex <= kRTX && ey >= 1 && ey <= kRTY;
-        double du = 0.0, dv = 0.0, dm = 0.0;
         if (l1 != T(0) || lb != T(0)) {
-            if (own) {
-                du = gu[i];
-                dv = gv[i];
-                dm = gm[i];
-            }
             if (own && l1 != T(0)) {
                 // wind and multiplier partials of stage 2 (weight dt/2 lam^{n+1})
-                const RhsGrad<T> r2 = stage_grad(a, B, x, y, u, v, gzx, gzy, cat, coef);
+                const RhsGrad<T> r2 = stage_grad5(a, b5, x, y, nin, coefs);
                 const T q2 = T(0.5) * T(a.dt) * l1;
                 du += (double)(q2 * r2.du);
                 dv += (double)(q2 * r2.dv);
                 dm += (double)(q2 * r2.dm);
             }
             if (lb != T(0)) {
-                const RhsGrad<T> r1 = stage_grad(a, P0, x, y, u, v, gzx, gzy, cat, coef);
+                const RhsGrad<T> r1 = stage_grad5(a, p5, x, y, nin, coefs);
                 const T q1 = T(a.dt) * lb;
                 Dp[0][ey][ex] = q1 * r1.dc;
                 Dp[1][ey][ex] = q1 * r1.dw;
@@ -755,38 +880,34 @@ k_rev_tile(const AdjArgs a2, const AdjArgs a1, int part1, int n1, const T *Di, c
         }
     }
     __syncthreads();
-    // ---- part 3 of step n, then part 1 of step n - 1, one tile node per thread
-    bool nz1 = false, nzp = false, nzt = false;
-    {
-        const int q = threadIdx.x;
-        const int ex = q % kRTX + 1, ey = q / kRTX + 1;
-        const int x = x0 + ex - 1, y = y0 + ey - 1;
-        int g3 = -1, g1 = -1;
-        double cx3 = 0.0, cy3 = 0.0, cx1 = 0.0, cy1 = 0.0;
-        if (q < kRTX * kRTY && x < nx && y < ny) {
-            const int i = y * nx + x;
-            const T gath = gather_lds(a, W, Dp, P0, x, y, ex, ey, x0, y0);
-            const T l = rev3_lds(a, i, x, y, L1i[i], W[ey][ex], gath, LP0, psi_n, ign, g3, cx3,
-                                 cy3);
-            T lo = l;
-            if (part1)
-                lo = rev1_node(a1, n1, i, x, y, l, set_step, psi_n1, P0n1, Bn1, psi_n, LT, LP0,
-                               u, v, gzx, gzy, cat, coef, ign, Do, g1, cx1, cy1);
-            L1o[i] = lo;
-            nz1 |= lo != T(0);
-            nzp |= LP0[i] != T(0);
-            nzt |= LT[i] != T(0);
+    // ---- part 3 of step n, then part 1 of step n - 1, at the tile's nodes
+    int g3 = -1, g1 = -1, vote = 0;
+    double cx3 = 0.0, cy3 = 0.0, cx1 = 0.0, cy1 = 0.0;
+    if (own) {
+        const T gath = gather_lds(a, W, Dp, P0, x, y, ex, ey, x0, y0);
+        T lo = rev3_lds(a, x, y, l5.c, W[ey][ex], gath, lp0, ps, ign, g3, cx3, cy3);
+        if (part1) {
+            const bool set = ss == n1;
+            lo = rev1_time(a1, set, x, y, lo, ps1, p01, ps, lt, lp0, ign, g1, cx1, cy1);
+            if (set) LT[i] = lt;
+            LP0[i] = lp0;
+            if (lo != T(0))
+                stage_D(stage_grad5(a1, q5, x, y, nin, coefs), i, n,
+                        T(0.5) * T(a1.dt) * lo, Do);
         }
-        shift_reduce_rt(g3, cx3, cy3, a.nign, acc, sh, t);
-        shift_reduce_rt(g1, cx1, cy1, a1.nign, acc, sh, t);
+        L1o[i] = lo;
+        vote = (lo != T(0) ? 1 : 0) | (lp0 != T(0) ? 2 : 0) | (lt != T(0) ? 4 : 0) |
+               (g3 >= 0 ? 8 : 0) | (g1 >= 0 ? 16 : 0);
     }
-    const int f1 = __syncthreads_or(nz1);
-    const int fp = __syncthreads_or(nzp);
-    const int ft = __syncthreads_or(nzt);
+    if (vote) atomicOr(&votes, vote);
+    __syncthreads();
+    const int got = votes;
+    if (got & 8) shift_reduce_rt(g3, cx3, cy3, a.nign, acc, sh, t);
+    if (got & 16) shift_reduce_rt(g1, cx1, cy1, a1.nign, acc, sh, t);
     if (threadIdx.x == 0) {
-        f_l1o[t] = f1;
-        fl.lp0[t] = fp;
-        fl.lt[t] = ft;
+        f_l1o[t] = got & 1;
+        fl.lp0[t] = got & 2;
+        fl.lt[t] = got & 4;
     }
 }
 
@@ -1141,7 +1262,8 @@ template <typename T> struct Run {
             AdjArgs ap = a;
             ap.t = part1 ? A->tstep[n_ - 1] : an.t;
             ap.ign_active = ign_active_at(ap.t);
-            hipLaunchKernelGGL(k_rev_tile<T>, dim3(nt), dim3(kRT), 0, s, an, ap, part1, n_ - 1,
+            hipLaunchKernelGGL(k_rev_tile<T>, dim3(nt), dim3(kRT),
+                               (size_t)c->ncat * kRevCoef * sizeof(T), s, an, ap, part1, n_ - 1,
                                (const T *)dbuf(cur), (const T *)l1buf(cur),
                                (const int32_t *)fl.l1[cur], (const T *)rb(p, k),
                                (const T *)rp0(p, k), (const T *)stack(p, k), LP0, l1buf(1 - cur),

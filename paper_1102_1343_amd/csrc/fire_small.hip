@@ -51,12 +51,17 @@ template <typename T> struct Node {
     int cv;
 };
 
+// i / w for 0 <= i < 2^16, 1 <= w < 2^12, r = 1 / w in float: (i + 1/2) / w is
+// at least 1 / (2 w) away from a whole number, far above the rounding.
+__device__ __forceinline__ int quot(int i, float r) { return (int)(((float)i + 0.5f) * r); }
+
 // Fills the ghost nodes of frame array P (pitch w, first node (fx0, fy0)).
 template <typename T>
 __device__ __forceinline__ void ghosts(T *P, int w, int h, int fx0, int fy0, int nx, int ny,
                                        bool corners, T *Q, T tp) {
+    const float rw = 1.0f / (float)w;
     for (int f = threadIdx.x; f < w * h; f += blockDim.x) {
-        const int fy = f / w, fx = f - fy * w;
+        const int fy = quot(f, rw), fx = f - fy * w;
         const int gx = fx0 + fx, gy = fy0 + fy;
         const bool xin = gx >= 0 && gx < nx, yin = gy >= 0 && gy < ny;
         if (xin && yin) continue;
@@ -86,6 +91,7 @@ __device__ __forceinline__ void small_tile(const StepArgs &a, const SmallPtrs<T>
     const int w = a.tile_x + 2 * kHalo, h = a.tile_y + 2 * kHalo, F = w * h;
     const int fx0 = x0 - kHalo, fy0 = y0 - kHalo;
     const int nt = blockDim.x, tid = threadIdx.x;
+    const float rw = 1.0f / (float)w, rw1 = 1.0f / (float)(w - 2);
     T *A = lds, *B = A + F, *C = B + F, *tab = C + F;   // frames, fuel table
     T *D = tab + a.ncat * kLRow;                        // latent flux of the tile
     int *flag = reinterpret_cast<int *>(D + a.tile_x * a.tile_y);
@@ -106,24 +112,24 @@ __device__ __forceinline__ void small_tile(const StepArgs &a, const SmallPtrs<T>
 #pragma unroll
     for (int k = 0; k < NF; k++) {
         const int f = tid + k * nt;
-        const int fy = f / w, fx = f - fy * w;
+        const int fy = quot(f, rw), fx = f - fy * w;
         const int gx = fx0 + fx, gy = fy0 + fy;
         pf[k] = f < F && gx >= 0 && gx < nx && gy >= 0 && gy < ny
-                    ? p.psi_in[(int64_t)gy * nx + gx] : T(0);
+                    ? p.psi_in[gy * nx + gx] : T(0);
     }
     Node<T> nd[NPT];
     const int w1 = w - 2, S1 = w1 * (h - 2);
 #pragma unroll
     for (int k = 0; k < NPT; k++) {
         const int i = tid + k * nt;
-        const int sy = i / w1, sx = i - sy * w1;
+        const int sy = quot(i, rw1), sx = i - sy * w1;
         Node<T> &n = nd[k];
         n.f = i < S1 ? (sy + 1) * w + sx + 1 : -1;
         n.gx = fx0 + 1 + sx;
         n.gy = fy0 + 1 + sy;
         n.in = i < S1 && n.gx >= 0 && n.gx < nx && n.gy >= 0 && n.gy < ny;
         if (n.in) {
-            const int64_t o = (int64_t)n.gy * nx + n.gx;
+            const int o = n.gy * nx + n.gx;   // (small meshes: below 2^31)
             n.cv = p.cat[o];
             n.u = p.u[o];
             n.v = p.v[o];
@@ -143,7 +149,7 @@ __device__ __forceinline__ void small_tile(const StepArgs &a, const SmallPtrs<T>
     for (int k = 0; k < NF; k++) {
         const int f = tid + k * nt;
         if (f >= F) break;
-        const int fy = f / w, fx = f - fy * w;
+        const int fy = quot(f, rw), fx = f - fy * w;
         T q = pf[k], tig = INF;
         for (int g = 0; g < a.nign; g++) {
             if (!itab->on[g]) continue;
@@ -192,7 +198,7 @@ __device__ __forceinline__ void small_tile(const StepArgs &a, const SmallPtrs<T>
                           n.gzy, row[k], c);
         const T pn = heun2(pn0, b0, hdt, f2);
         A[n.f] = pn;   // stage-1 reads of A ended at the last barrier
-        const int64_t o = (int64_t)n.gy * nx + n.gx;
+        const int o = n.gy * nx + n.gx;   // (small meshes: below 2^31)
         if (REC) {
             if (mine) {
                 p.psi_out[o] = pn;
@@ -260,7 +266,7 @@ __device__ __forceinline__ void small_tile(const StepArgs &a, const SmallPtrs<T>
                 const T dF = (n.fr - Fn) * rdt;
                 fs = dF * row[k][kLCh];
                 fl = dF * row[k][kLCq];
-                if (!(Fn == n.fr)) p.frac[(int64_t)n.gy * nx + n.gx] = Fn;
+                if (!(Fn == n.fr)) p.frac[n.gy * nx + n.gx] = Fn;
                 if (!__builtin_isfinite(Fn)) st |= kStNonfinite;
                 hot = true;
             }
