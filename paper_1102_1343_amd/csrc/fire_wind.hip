@@ -35,8 +35,9 @@ constexpr int kWB = 256;
 
 struct WindArgs {
     int32_t nax, nay, nz, sr_x, sr_y, nx, ny;
-    int32_t vec;       // rows of 4k cells and 4-element-aligned outputs: vector stores
+    int32_t vec;       // every row of both outputs starts on 16 bytes: vector stores
     double zf, g;
+    int32_t nchunk;    // kWChunk-cell chunks of a fire row
     double lzf;        // ln z_f
     double rsx, rsy;   // 1 / sr_x, 1 / sr_y
 };
@@ -151,89 +152,105 @@ template <typename T> __device__ __forceinline__ Axis<T> axis(int N, int Dn, T r
     return r;
 }
 
-// A work-group takes kWChunk consecutive cells of kWRows consecutive fire
-// rows.  Per row the y-interpolation is done once per staggered point the
-// chunk spans, into a line in LDS (the y weights are the same along the row;
-// two lines alternate, so one barrier per row suffices); each thread then
-// interpolates its 4 consecutive cells in x from that line, with the x
-// positions and weights formed once for all the rows, and, when rows are
-// 4-aligned, stores them as one 16-byte non-temporal vector.  A fire centre
-// is at x/DX = (i + 1/2)/sr_x; u-points at (I, J + 1/2), v-points at
+// A work-group takes kWChunk consecutive cells of kWRows consecutive fire rows
+// of one component.  Per row the y-interpolation is done once per staggered
+// point the chunk spans, into a line in LDS (the y weights are the same along
+// the row; two lines alternate, so one barrier per row suffices); each thread
+// then interpolates its 4 cells in x from that line, with the x positions and
+// weights formed once for all the rows.  When rows start on 16 bytes, a store
+// is 16 bytes of each lane, non-temporal, 1 KiB in a row of a wave: 4 cells in
+// FP32, 2 in FP64 (the FP64 lane's other two lie half a chunk on).  A fire
+// centre is at x/DX = (i + 1/2)/sr_x; u-points at (I, J + 1/2), v-points at
 // (I + 1/2, J) in atmosphere-cell units.  Arithmetic in the array precision.
+//
+// Bound by the stores of the two outputs.  With both components in one
+// work-group of 8 rows and 32 bytes of a lane in FP64, the two streams met in
+// the same memory channels where a row is a power of two, and FP64 stores left
+// half lines; call times, before -> now: 8192^2 FP32 115.3 -> 98 us (5.5 TB/s
+// of output), FP64 518 -> 224 us; 4000^2 FP32 51.6 -> 50.0 us, FP64 90.5 -> 52.4
+// us; 397x301 FP64 15.0 -> 7.6 us (the chain of a work-group's rows).  Rows of
+// a work-group at 8192^2 FP32: 1: 158 us (the x positions are then formed for
+// every row), 2: 111, 3: 98, 4: 109, 6: 114: bands of an odd number of rows keep
+// work-groups at work together off each other's channels.
 constexpr int kWChunk = 4 * kWB;
-constexpr int kWRows = 8;
+constexpr int kWRows = 3;
 // staggered points a chunk can span: (kWChunk - 1)/sr_x + 3 at most
 constexpr int kWLine = kWChunk + 4;
 
-template <typename T> using W4 = T __attribute__((ext_vector_type(4)));
+// cells of one 16-byte store
+template <typename T> constexpr int kWVec = 16 / (int)sizeof(T);
+template <typename T> using WV = T __attribute__((ext_vector_type(kWVec<T>)));
 
+// One component of the work-group's rows: nk x nl staggered points pf, fire
+// centre i at (2i + 1 - sx) / (2 sr_x) in them, row j at (2j + 1 - sy) / (2 sr_y).
 template <typename T>
-__global__ void __launch_bounds__(kWB)
-k_wind_bilinear(const WindArgs a, const T *uf, const T *vf, T *u, T *v) {
-    __shared__ T Lu[2][kWLine], Lv[2][kWLine];
-    // row bands along x (up to 2^21 of them), chunks along y (up to 2^14)
-    const int j0 = blockIdx.x * kWRows;
-    const int c0 = blockIdx.y * kWChunk;
+__device__ __forceinline__ void wind_rows(const WindArgs &a, const T *pf, T *out, int nk, int nl,
+                                          int sx, int sy, int j0, int c0, T (*L)[kWLine]) {
     const int Dx = 2 * a.sr_x, Dy = 2 * a.sr_y;
     const T rx = T(a.rsx) * T(0.5), ry = T(a.rsy) * T(0.5);
-    // x/DX = (2i + 1) / (2 sr_x), shifted by -1/2 (= -sr_x / (2 sr_x)) for v;
-    // point ranges [ub, ue], [vb, ve] of the chunk's cells
+    // point range [pb, pe] of the chunk's cells
     const int c1 = (c0 + kWChunk < a.nx ? c0 + kWChunk : a.nx) - 1;
-    const int ub = axis(2 * c0 + 1, Dx, rx, a.nax + 1).k0;
-    const int ue = axis(2 * c1 + 1, Dx, rx, a.nax + 1).k1;
-    const int vb = axis(2 * c0 + 1 - a.sr_x, Dx, rx, a.nax).k0;
-    const int ve = axis(2 * c1 + 1 - a.sr_x, Dx, rx, a.nax).k1;
+    const int pb = axis(2 * c0 + 1 - sx, Dx, rx, nk).k0;
+    const int pe = axis(2 * c1 + 1 - sx, Dx, rx, nk).k1;
     // this thread's cells: line positions and weights, the same in every row
-    const int i0 = c0 + 4 * threadIdx.x;
-    int uk0[4], uk1[4], vk0[4], vk1[4];
-    T ut[4], vt[4];
+    constexpr int V = kWVec<T>, G = 4 / V;
+    const int i0 = c0 + V * threadIdx.x;
+    int k0[4], k1[4];
+    T t[4];
 #pragma unroll
     for (int q = 0; q < 4; q++) {
-        const int i = i0 + q < a.nx ? i0 + q : a.nx - 1;
-        const Axis<T> ux = axis(2 * i + 1, Dx, rx, a.nax + 1);
-        const Axis<T> vx = axis(2 * i + 1 - a.sr_x, Dx, rx, a.nax);
-        uk0[q] = ux.k0 - ub;
-        uk1[q] = ux.k1 - ub;
-        ut[q] = ux.t;
-        vk0[q] = vx.k0 - vb;
-        vk1[q] = vx.k1 - vb;
-        vt[q] = vx.t;
+        const int c = i0 + (q / V) * (V * kWB) + q % V;
+        const Axis<T> x = axis(2 * (c < a.nx ? c : a.nx - 1) + 1 - sx, Dx, rx, nk);
+        k0[q] = x.k0 - pb;
+        k1[q] = x.k1 - pb;
+        t[q] = x.t;
     }
     const bool vec = a.vec != 0;
     const int j1 = j0 + kWRows < a.ny ? j0 + kWRows : a.ny;
     int p = 0;
     for (int j = j0; j < j1; j++, p ^= 1) {
-        const Axis<T> uy = axis(2 * j + 1 - a.sr_y, Dy, ry, a.nay);
-        const Axis<T> vy = axis(2 * j + 1, Dy, ry, a.nay + 1);
-        const T *u0 = uf + (size_t)uy.k0 * (a.nax + 1), *u1 = uf + (size_t)uy.k1 * (a.nax + 1);
-        const T *v0 = vf + (size_t)vy.k0 * a.nax, *v1 = vf + (size_t)vy.k1 * a.nax;
+        const Axis<T> y = axis(2 * j + 1 - sy, Dy, ry, nl);
+        const T *p0 = pf + (size_t)y.k0 * nk, *p1 = pf + (size_t)y.k1 * nk;
         // (line p was last read in row j - 2, before every thread reached the
         // barrier of row j - 1)
-        for (int q = threadIdx.x; q <= ue - ub && q < kWLine; q += kWB)
-            Lu[p][q] = (T(1) - uy.t) * u0[ub + q] + uy.t * u1[ub + q];
-        for (int q = threadIdx.x; q <= ve - vb && q < kWLine; q += kWB)
-            Lv[p][q] = (T(1) - vy.t) * v0[vb + q] + vy.t * v1[vb + q];
+        for (int q = threadIdx.x; q <= pe - pb && q < kWLine; q += kWB)
+            L[p][q] = (T(1) - y.t) * p0[pb + q] + y.t * p1[pb + q];
         __syncthreads();
-        if (i0 < a.nx) {
-            T ou[4], ov[4];
+        T *row = out + (size_t)j * a.nx;
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
-                ou[q] = (T(1) - ut[q]) * Lu[p][uk0[q]] + ut[q] * Lu[p][uk1[q]];
-                ov[q] = (T(1) - vt[q]) * Lv[p][vk0[q]] + vt[q] * Lv[p][vk1[q]];
-            }
-            const size_t row = (size_t)j * a.nx;
-            if (vec) {   // streaming (non-temporal) stores: the output is not re-read here
-                const W4<T> wu = {ou[0], ou[1], ou[2], ou[3]}, wv = {ov[0], ov[1], ov[2], ov[3]};
-                __builtin_nontemporal_store(wu, reinterpret_cast<W4<T> *>(u + row + i0));
-                __builtin_nontemporal_store(wv, reinterpret_cast<W4<T> *>(v + row + i0));
-            } else {
-                for (int q = 0; q < 4 && i0 + q < a.nx; q++) {
-                    u[row + i0 + q] = ou[q];
-                    v[row + i0 + q] = ov[q];
+        for (int g = 0; g < G; g++) {
+            const int c = i0 + g * (V * kWB);
+            if (c < a.nx) {
+                WV<T> o;
+#pragma unroll
+                for (int q = 0; q < V; q++) {
+                    const int r = g * V + q;
+                    o[q] = (T(1) - t[r]) * L[p][k0[r]] + t[r] * L[p][k1[r]];
                 }
+                if (vec)   // streaming (non-temporal) stores: the output is not re-read here
+                    __builtin_nontemporal_store(o, reinterpret_cast<WV<T> *>(row + c));
+                else
+#pragma unroll
+                    for (int q = 0; q < V; q++)
+                        if (c + q < a.nx) row[c + q] = o[q];
             }
         }
     }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kWB)
+k_wind_bilinear(const WindArgs a, const T *uf, const T *vf, T *u, T *v) {
+    __shared__ T L[2][kWLine];
+    // along x the chunks of a band of rows in turn (up to 2^23 work-groups),
+    // the components along z: u is written whole, then v
+    const int band = blockIdx.x / a.nchunk;
+    const int j0 = band * kWRows;
+    const int c0 = (blockIdx.x - band * a.nchunk) * kWChunk;
+    if (blockIdx.z == 0)
+        wind_rows(a, uf, u, a.nax + 1, a.nay, 0, a.sr_y, j0, c0, L);
+    else
+        wind_rows(a, vf, v, a.nax, a.nay + 1, a.sr_x, 0, j0, c0, L);
 }
 
 bool grid_ok(const fire_wind_grid *g) {
@@ -266,10 +283,10 @@ hipError_t run(const fire_wind_grid *g, const void *u3, const void *v3, const vo
     a.sr_y = g->sr_y;
     a.nx = g->nx;
     a.ny = g->ny;
-    a.vec = (g->nx % 4 == 0) && ((uintptr_t)u % (4 * sizeof(T)) == 0) &&
-            ((uintptr_t)v % (4 * sizeof(T)) == 0);
+    a.vec = (g->nx % kWVec<T> == 0) && ((uintptr_t)u % 16 == 0) && ((uintptr_t)v % 16 == 0);
     a.zf = g->zf;
     a.g = g->g;
+    a.nchunk = (g->nx + kWChunk - 1) / kWChunk;
     a.lzf = std::log(g->zf);
     a.rsx = 1.0 / g->sr_x;   // 1/(2 sr) = rs / 2 is exact in binary
     a.rsy = 1.0 / g->sr_y;
@@ -280,7 +297,7 @@ hipError_t run(const fire_wind_grid *g, const void *u3, const void *v3, const vo
                        (const T *)u3, (const T *)v3, (const T *)phi, (const T *)hgt,
                        (const T *)z0, uf, vf);
     hipLaunchKernelGGL(k_wind_bilinear<T>,
-                       dim3((g->ny + kWRows - 1) / kWRows, (g->nx + kWChunk - 1) / kWChunk),
+                       dim3((unsigned)((g->ny + kWRows - 1) / kWRows) * (unsigned)a.nchunk, 1, 2),
                        dim3(kWB), 0, s, a, (const T *)uf, (const T *)vf, (T *)u, (T *)v);
     return hipGetLastError();
 }

@@ -102,3 +102,23 @@ def test_wind_8192_sampled():
     assert scale > 1.0
     assert err <= 2e-6 * scale
     assert np.isfinite(u_g).all() and np.isfinite(v_g).all()
+
+
+@pytest.mark.parametrize("dt", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("nx,ny", [(1024, 4), (1026, 5), (1027, 9), (1536, 3), (2, 1)])
+def test_outputs_at_any_element_get_the_same_values(dt, nx, ny):
+    """Vector and scalar stores, rows of part chunks, part bands of rows."""
+    sr = 4
+    nax, nay = -(-nx // sr), -(-ny // sr)
+    atm = synth.atmosphere(nax, nay, nz=3, dx=24.0, dy=24.0, seed=nx)
+    args = [_dev(atm[k], dt) for k in ("u3", "v3", "phi", "hgt", "z0")]
+    want = F.wind_interp(*args, nx, ny, sr, sr)
+    n = nx * ny
+    for off in (1, 2, 4):
+        flat = [torch.full((n + 8,), -77.0, dtype=dt, device="cuda") for _ in range(2)]
+        out = tuple(f[off:off + n].view(ny, nx) for f in flat)
+        F.wind_interp(*args, nx, ny, sr, sr, out=out)
+        torch.cuda.synchronize()
+        for w, o, f in zip(want, out, flat):
+            assert torch.equal(o, w), (nx, ny, off)
+            assert (f[:off] == -77.0).all() and (f[off + n:] == -77.0).all()
