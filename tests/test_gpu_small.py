@@ -82,3 +82,34 @@ def test_small_tiles_keep_nan_and_infinity():
     for x, y in zip(res[0][:5], res[1][:5]):
         assert torch.equal(torch.nan_to_num(x, nan=12345.0), torch.nan_to_num(y, nan=12345.0))
     assert res[0][5] == res[1][5] and res[0][5] & F.STATUS_NONFINITE
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("fire", [True, False], ids=["one-node-burns", "one-cell-lost-fuel"])
+def test_tiles_with_one_active_node(dtype, fire):
+    """A tile without flux skips the fuel fraction; the small tiles share the
+    cells out differently, so both agree only if every tile that one node at
+    its corner, edge or ring makes active is taken as active."""
+    nx, ny = 250, 45
+    prob = _problem(nx, ny, 10, 5)
+    prob.ignitions = []
+    u, v = (torch.from_numpy(a).to("cuda", dtype) for a in prob.wind[0])
+    for x, y in ((119, 19), (120, 20), (119, 20), (60, 0), (0, 10), (249, 44), (121, 41), (1, 1)):
+        res = []
+        for tile in (None, (120, 20)):
+            f = F.Fire.from_problem(prob, dtype=dtype)
+            if tile:
+                f.set_tile(*tile)
+            psi = torch.full((ny, nx), 40.0, device="cuda", dtype=dtype)
+            frac = torch.ones_like(psi)
+            tign = torch.full_like(psi, math.inf)
+            if fire:
+                psi[y, x], tign[y, x] = -3.0, -1.0
+            else:
+                frac[y, x] = 0.5
+            f.set_state(psi, tign, frac, 0.0)
+            out = f.step(u, v, prob.dt)
+            res.append([f.psi.clone(), f.tign.clone(), f.frac.clone(), *out])
+        for a, b in zip(*res):
+            assert torch.equal(a, b), (x, y)
+        assert bool((res[0][3] != 0).any()), (x, y)
