@@ -141,28 +141,6 @@ __device__ __forceinline__ T ros_row(const lds_t<T> *row, T un, T tn, T cap) {
     return ros_v4(r0, r1, un, tn, cap);
 }
 
-// A table row's spread-rate entries in registers.
-template <typename T> struct RosRow {
-    V4<T> r0;       // R0 c d b
-    T e, floor;
-};
-template <typename T> __device__ __forceinline__ RosRow<T> read_row(const lds_t<T> *row) {
-    const lds_t<V4<T>> *q = reinterpret_cast<const lds_t<V4<T>> *>(row);
-    RosRow<T> r;
-    r.r0.x = q[0].x; r.r0.y = q[0].y; r.r0.z = q[0].z; r.r0.w = q[0].w;
-    r.e = q[1].x;
-    r.floor = q[1].y;
-    return r;
-}
-template <typename T>
-__device__ __forceinline__ T ros_row(const RosRow<T> &row, T un, T tn, T cap) {
-    V4<T> r1;
-    r1.x = row.e;
-    r1.y = row.floor;
-    r1.z = r1.w = T(0);
-    return ros_v4(row.r0, r1, un, tn, cap);
-}
-
 // Right-hand side of Eq. (12) at a node from its value pc and its four
 // neighbours (west, east, south, north).  The Godunov choice of Eq. (13)
 // enters only through its square, which for every sign pattern is
@@ -173,7 +151,7 @@ __device__ __forceinline__ T ros_row(const RosRow<T> &row, T un, T tn, T cap) {
 // mirror the inner nodes -- whatever the compiler fuses.
 // Every product that is fused with a sum is written as a fused multiply-add
 // and contraction is off, so each kernel that calls this (the tiled step, the
-// streamed step, the replays) gets the same bits.
+// small-tile step, the replays) gets the same bits.
 template <typename T, typename RowPtr>
 __device__ __forceinline__ T rhs5(T pc, T pw, T pe, T ps, T pn, T u, T v, T gzx, T gzy,
                                   RowPtr row, const Consts<T> &c) {

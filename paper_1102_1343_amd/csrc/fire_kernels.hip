@@ -155,7 +155,7 @@ __device__ __forceinline__ T cell_fraction(const T (*A)[kFW], int fy, const T (*
 // domain's step); otherwise it is formed here from the geometry table.
 template <typename T, int KR, bool SMALL, bool REC, bool PRE>
 __device__ __forceinline__ void
-step_tile(const StepArgs &a, const int tile, const int tx, const int ty, const uint32_t cbase,
+step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const uint32_t cbase,
           const double tnow,
           const IgnTable<T> *itab, const T *__restrict__ psi_in, T *__restrict__ psi_out, T *tign, T *frac,
           const T *__restrict__ uw, const T *__restrict__ vw, const T *__restrict__ dzdx,
@@ -163,6 +163,12 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int ty, const u
           T *__restrict__ fsens, T *__restrict__ flat, int *status, T *rec_p0, T *rec_b,
           int32_t *mark, const uint32_t *__restrict__ iuse, const T *__restrict__ ilb,
           const T *__restrict__ irow) {
+    // A wave's 64 lanes share one frame row: in a scalar register, the row's
+    // range tests and LDS row offsets cost no vector work, which is what this
+    // kernel is short of (84 % of the cycles of an unburnt 8192^2 step), and
+    // the FP32 120 x 20 kernel needs 60 vector registers without a spill.
+    // Per step: 8192^2 541 -> 528 us, 4099x4001 with fires 183 -> 179 us.
+    const int ty = __builtin_amdgcn_readfirstlane(tyv);
     constexpr int FHM = kNR * KR;
     __shared__ T A[FHM][kFW];
     __shared__ T B[FHM - 2][kFW];
