@@ -432,13 +432,20 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     };
     auto src2 = [&](int k) { return in2(k) ? idx0 + roff(k) : cbase; };
     nxt = load_inputs<SMALL>(src2(0), cat, uw, vw, dzdx, dzdy);
+    // F^n of row k + 1, loaded with its inputs (loaded and tested in the same
+    // row, the test also waits for the next row's inputs: 4099x4001 with fires
+    // 179 -> 175 us a step, 700^2 FP32 19.9 -> 19.3)
+    T fo1 = T(1);
+    if (!REC) fo1 = at<SMALL>(frac, src2(0));
 #pragma unroll
     for (int k = 0; k < KR; k++) {
         const int fy = ty + kNR * k;
         const Inputs<T> cur = nxt;
-        T fo = T(1);
-        if (!REC) fo = at<SMALL>(frac, src2(k));
-        if (k + 1 < KR) nxt = load_inputs<SMALL>(src2(k + 1), cat, uw, vw, dzdx, dzdy);
+        const T fo = fo1;
+        if (k + 1 < KR) {
+            nxt = load_inputs<SMALL>(src2(k + 1), cat, uw, vw, dzdx, dzdy);
+            if (!REC) fo1 = at<SMALL>(frac, src2(k + 1));
+        }
         if (in2(k)) {
             const int gy = y0 - kHalo + fy;
             const uint32_t idx = idx0 + roff(k);
