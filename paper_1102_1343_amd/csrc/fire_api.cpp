@@ -92,7 +92,10 @@ void ignition_window(const fire_ignition *ign, int n, double *lo, double *hi) {
 // FP32 7.6 / 17, FP64 9.3 / 35; 300^2 8.6 / 17, 14 / 35; 600^2 14.6 / 17.8,
 // 32 / 36; 700^2 15.7-22.6 / 18-20, 39 / 39; 800^2 18-24 / 18-20, 47 / 47;
 // 1000^2 25 / 21, 65 / 51 (the rings computed twice and the waves' number
-// cost more than the latency saves): the line is at 400 000 cells.
+// cost more than the latency saves): the line is at 400 000 cells.  One FP32
+// mesh takes them up to 650 000: 660^2 12.4-15.0 / 18.9, 700^2 14.7-15.8 / 19.3
+// (17.0 / 24.4 while four lines grow), 780^2 16.4-17.1 / 19.1, 860^2 18.0-20.3 /
+// 21.7, 960^2 23.2-25.3 / 21.8.
 // The tile is the smallest of whole atmosphere cells, at least 8 cells a
 // side, that gives at most 700 work-groups (256 CUs, two or three each).
 StepKind step_kind(const fire_mesh *m, int ndom, int *tx, int *ty) {
@@ -102,7 +105,7 @@ StepKind step_kind(const fire_mesh *m, int ndom, int *tx, int *ty) {
     // nodes of a tile with its two inner rings: two per thread, and LDS of at
     // most 64 KiB with 256 fuels
     const int most = m->dtype == FIRE_F64 ? 1024 : 2048;
-    if (cells <= kSmallCells) {
+    if (cells <= (ndom == 1 && m->dtype == FIRE_F32 ? kSmallCells32 : kSmallCells)) {
         int x = (8 + sx - 1) / sx * sx, y = (8 + sy - 1) / sy * sy;
         for (;;) {
             int64_t n = 0;

@@ -210,6 +210,7 @@ bool tile_ok(const fire_mesh *m, int tile_x, int tile_y);
 // the step kernels, and the one for these meshes when no tile shape was chosen
 enum StepKind { kTiled, kSmall };
 constexpr int64_t kSmallCells = 400000;   // cells in all that take the small tiles
+constexpr int64_t kSmallCells32 = 650000; // the same of one FP32 mesh
 StepKind step_kind(const fire_mesh *m, int ndom, int *tx, int *ty);
 // [lo, hi] outside which none of the ignitions is active (the activity test
 // of the step kernel, in the same double arithmetic); lo > hi when n = 0.

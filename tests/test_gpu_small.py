@@ -113,3 +113,13 @@ def test_tiles_with_one_active_node(dtype, fire):
         for a, b in zip(*res):
             assert torch.equal(a, b), (x, y)
         assert bool((res[0][3] != 0).any()), (x, y)
+
+
+@pytest.mark.parametrize("nx,ny,sr_x,sr_y", [(807, 805, 8, 5), (807, 806, 10, 10)])
+def test_largest_small_single_precision_mesh_and_the_next(nx, ny, sr_x, sr_y):
+    prob = _problem(nx, ny, sr_x, sr_y)
+    a = _run(prob, torch.float32, None)
+    b = _run(prob, torch.float32, (120, 20))
+    for x, y in zip(a[:-1], b[:-1]):
+        assert torch.equal(x, y)
+    assert a[-1] == b[-1]
