@@ -92,6 +92,17 @@ __device__ __forceinline__ int phase_copy(int v) {
     return v;
 }
 
+// Rows k in [k0, k1) of a wave (frame rows ty + kNR k) that lie in the frame
+// rows [lo, hi).
+struct Rows {
+    int k0, k1;
+};
+__device__ __forceinline__ Rows phase_rows(int ty, int lo, int hi) {
+    static_assert(kNR == 4, "row strides of a thread");
+    const int t = phase_copy(ty);
+    return {(lo - t + kNR - 1) >> 2, (hi - t + kNR - 1) >> 2};
+}
+
 // Lane permutations within each row of 16 lanes (DPP): swap neighbours,
 // swap pairs, mirror each half row, mirror the row.  A lane whose source is
 // unavailable keeps its own value.
@@ -217,7 +228,8 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
 
     for (int i = tid; i < a.ncat; i += kBlock)
         make_row(coef + i * kNCoef, tab + i * kLRow, T(a.ros_cap));
-    // set where a node of the tile or its ring burns or has lost fuel
+    // set where a node of the tile or its ring burns or a cell of the tile has
+    // lost fuel
     __shared__ int active;
     constexpr int kStActive = 1 << 30;   // the same in a thread's status
     if (!REC && tid == 0) active = 0;
@@ -391,10 +403,8 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     // the per-cell inputs of row k + 1 are loaded while row k computes
     // (rows outside the stage load the domain's first cell instead, unused:
     // unconditional loads need no register copies)
-    auto in1 = [&](int k) {
-        const int fy = ty + kNR * k;
-        return xr1 && fy >= lo1 && fy < hi1;
-    };
+    const Rows r1 = phase_rows(ty, lo1, hi1);
+    auto in1 = [&](int k) { return xr1 && k >= r1.k0 && k < r1.k1; };
     auto src1 = [&](int k) { return in1(k) ? idx0 + roff(k) : cbase; };
     Inputs<T> nxt = load_inputs<SMALL>(src1(0), cat, uw, vw, dzdx, dzdy);
 #pragma unroll
@@ -426,17 +436,19 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     // node times t^ = t' where psi^{n+1} >= 0, else t_i (Eq. 17)
     int st = 0;
     const int gw = a.guard;
-    auto in2 = [&](int k) {
-        const int fy = ty + kNR * k;
-        return xr2 && fy >= lo2 && fy < hi2;
-    };
+    const Rows r2 = phase_rows(ty, lo2, hi2), r3 = phase_rows(ty, lo3, hi3);
+    auto in2 = [&](int k) { return xr2 && k >= r2.k0 && k < r2.k1; };
     auto src2 = [&](int k) { return in2(k) ? idx0 + roff(k) : cbase; };
     nxt = load_inputs<SMALL>(src2(0), cat, uw, vw, dzdx, dzdy);
-    // F^n of row k + 1, loaded with its inputs (loaded and tested in the same
-    // row, the test also waits for the next row's inputs: 4099x4001 with fires
-    // 179 -> 175 us a step, 700^2 FP32 19.9 -> 19.3)
+    // F^n of row k + 1 at the tile's own cells, loaded with its inputs (loaded
+    // and tested in the same row, the test also waits for the next row's
+    // inputs: 4099x4001 with fires 179 -> 175 us a step, 700^2 FP32 19.9 ->
+    // 19.3).  A ring cell's F belongs to another work-group, which may be
+    // writing it; it matters to neither F nor the fluxes here.
+    auto in3 = [&](int k) { return xr3 && k >= r3.k0 && k < r3.k1; };
+    auto src3 = [&](int k) { return in3(k) ? idx0 + roff(k) : cbase; };
     T fo1 = T(1);
-    if (!REC) fo1 = at<SMALL>(frac, src2(0));
+    if (!REC) fo1 = at<SMALL>(frac, src3(0));
 #pragma unroll
     for (int k = 0; k < KR; k++) {
         const int fy = ty + kNR * k;
@@ -444,7 +456,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
         const T fo = fo1;
         if (k + 1 < KR) {
             nxt = load_inputs<SMALL>(src2(k + 1), cat, uw, vw, dzdx, dzdy);
-            if (!REC) fo1 = at<SMALL>(frac, src2(k + 1));
+            if (!REC) fo1 = at<SMALL>(frac, src3(k + 1));
         }
         if (in2(k)) {
             const int gy = y0 - kHalo + fy;
@@ -466,14 +478,15 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
             }
             if (!REC) {
                 C[fy - 2][tx] = pn >= T(0) ? tp : ti;
-                if (!(pn >= T(0) && fo == T(1))) st |= kStActive;
+                if (!(pn >= T(0))) st |= kStActive;
             }
-            if (xr3 && fy >= 3 && fy < a.tile_y + 3) {
+            if (in3(k)) {
                 at<SMALL>(psi_out, idx) = pn;
                 if (REC) {   // psi' and psi* of the step, for the reverse pass
                     at<SMALL>(rec_p0, idx) = pn0;
                     at<SMALL>(rec_b, idx) = B[fy - 1][tx];
                 } else {
+                    if (!(fo == T(1))) st |= kStActive;
                     if (!(ti == told)) {
                         at<SMALL>(tign, idx) = ti;
                         // the step in which t_i was first set
@@ -492,7 +505,8 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     st &= ~kStActive;
     __syncthreads();
     // No node of the tile and its ring has psi < 0 (a ghost is never below its
-    // domain node) and every cell has F = 1: F stays, the fluxes are zero.
+    // domain node) and every cell of the tile has F = 1: F stays, the fluxes
+    // are zero.
     // A landscape's tiles are mostly of this kind, and the nine-node minimum,
     // the flux frames and their sums, with four barriers, are LDS work that the
     // memory waits do not hide: per step 8192^2 FP32 572 -> 541 us (20 steps
@@ -533,21 +547,19 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     // burning sub-cell point: beta = 0 in every sub-cell and F = 1 exactly.
     // The sensible flux goes straight to B (not read in this phase).
     T fl[KR];
-    auto in3 = [&](int k) {
-        const int fy = ty + kNR * k;
-        return xr3 && fy >= lo3 && fy < hi3;
-    };
-    auto src3 = [&](int k) { return in3(k) ? idx0 + roff(k) : cbase; };
+    const Rows r4 = phase_rows(ty, lo3, hi3);
+    auto in4 = [&](int k) { return xr3 && k >= r4.k0 && k < r4.k1; };
+    auto src4 = [&](int k) { return in4(k) ? idx0 + roff(k) : cbase; };
     // F of row k + 1 is loaded while row k computes
-    T fo_next = at<SMALL>(frac, src3(0));
+    T fo_next = at<SMALL>(frac, src4(0));
 #pragma unroll
     for (int k = 0; k < KR; k++) {
         const int fy = ty + kNR * k;
         T fs = T(0);
         fl[k] = T(0);
         const T fo = fo_next;
-        if (k + 1 < KR) fo_next = at<SMALL>(frac, src3(k + 1));
-        if (in3(k)) {
+        if (k + 1 < KR) fo_next = at<SMALL>(frac, src4(k + 1));
+        if (in4(k)) {
             const uint32_t idx = idx0 + roff(k);
             T mn = vmin(vmin(A[fy - 1][tx - 1], A[fy - 1][tx]), A[fy - 1][tx + 1]);
             mn = vmin(mn, vmin(vmin(A[fy][tx - 1], A[fy][tx]), A[fy][tx + 1]));

@@ -137,7 +137,11 @@ __device__ __forceinline__ void small_tile(const StepArgs &a, const SmallPtrs<T>
             n.gzy = p.gy[o];
             if (!REC) {
                 n.ti = p.tign[o];
-                n.fr = p.frac[o];
+                // a ring cell's F belongs to another work-group, which may be
+                // writing it: the tile's first cell in its place (unused)
+                const bool mine = (uint32_t)(n.gx - x0) < (uint32_t)a.tile_x &&
+                                  (uint32_t)(n.gy - y0) < (uint32_t)a.tile_y;
+                n.fr = p.frac[mine ? o : y0 * nx + x0];
             }
         }
     }
