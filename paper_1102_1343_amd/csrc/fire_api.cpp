@@ -219,6 +219,7 @@ hipError_t step_raw(fire_ctx *c, const void *psi_in, void *psi_out, void *tign, 
     a.rdy = 1.0 / m.dy;
     a.t = t;
     a.dt = dt;
+    a.rdt = 1.0 / dt;
     a.eps = c->prm.viscosity;
     a.ros_cap = c->prm.ros_cap;
 

@@ -284,6 +284,7 @@ int fire_ens_step(fire_ens *e, const void *u, const void *v, double dt, void *fl
     a.guard = e->prm.guard_width;
     a.visc_mode = e->prm.viscosity_mode;
     a.dt = dt;
+    a.rdt = 1.0 / dt;
     a.eps = e->prm.viscosity;
     a.ros_cap = e->prm.ros_cap;
     StepBuffers b;

@@ -43,6 +43,7 @@ struct StepArgs {
     double dx, dy;
     double rdx, rdy;     // 1/dx, 1/dy
     double t, dt;        // t unused by the ensemble kernel (device time)
+    double rdt;          // 1/dt
     double eps, ros_cap;
 };
 

@@ -84,11 +84,18 @@ __device__ __forceinline__ void ghost_node(T (*P)[kFW], int fy, int fx, int gx, 
 }
 
 // A copy of a wave-uniform value that the compiler cannot see through.  The
-// step takes one per phase for the frame-row bounds, so the per-row range
-// masks formed from them are not shared between phases (held across the
-// kernel, they would be spilled and reloaded row by row).
+// step takes one per phase for the frame-row bounds and the wave's frame row,
+// so the per-row range masks and row numbers formed from them are not shared
+// between phases (held across the kernel, they would be spilled and reloaded
+// row by row).  Not volatile, so copies do not order the code around them
+// (256-member ensemble 8470 -> 8428 us over 8 steps).
 __device__ __forceinline__ int phase_copy(int v) {
-    asm volatile("" : "+s"(v));
+    asm("" : "+s"(v));
+    return v;
+}
+// The same for a lane's value, so that masks formed from it are not shared.
+__device__ __forceinline__ int lane_copy(int v) {
+    asm("" : "+v"(v));
     return v;
 }
 
@@ -98,7 +105,6 @@ struct Rows {
     int k0, k1;
 };
 __device__ __forceinline__ Rows phase_rows(int ty, int lo, int hi) {
-    static_assert(kNR == 4, "row strides of a thread");
     const int t = phase_copy(ty);
     return {(lo - t + kNR - 1) >> 2, (hi - t + kNR - 1) >> 2};
 }
@@ -176,9 +182,14 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
           const T *__restrict__ irow) {
     // A wave's 64 lanes share one frame row: in a scalar register, the row's
     // range tests and LDS row offsets cost no vector work, which is what this
-    // kernel is short of (84 % of the cycles of an unburnt 8192^2 step), and
-    // the FP32 120 x 20 kernel needs 60 vector registers without a spill.
-    // Per step: 8192^2 541 -> 528 us, 4099x4001 with fires 183 -> 179 us.
+    // kernel is short of (84 % of the cycles of an unburnt 8192^2 step).  Each
+    // phase forms them, and the masks of the lanes' columns, from copies of
+    // its own: shared between the phases, they do not fit the scalar registers
+    // of 8 waves per SIMD (30 spills in the FP32 120 x 20 kernel, two to four
+    // reloads from vector lanes in every row of the edge tiles' passes and of
+    // stage 2; with the copies 11, outside the row loops, 60 vector registers).
+    // Per step, vector row -> scalar row -> copies: 8192^2 556 -> 520 -> 517 us,
+    // 4099x4001 with fires 181 -> 179 -> 176 us, 2048^2 41.4 -> 39.2 -> 37.8 us.
     const int ty = __builtin_amdgcn_readfirstlane(tyv);
     constexpr int FHM = kNR * KR;
     __shared__ T A[FHM][kFW];
@@ -196,10 +207,10 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     const int nx = a.nx, ny = a.ny;
     const int FH = a.tile_y + 2 * kHalo;
     const int gx = x0 - kHalo + tx;
-    const bool colin = gx >= 0 && gx < nx;
-    const bool xr1 = colin && tx >= 1 && tx < a.tile_x + 5;
-    const bool xr2 = colin && tx >= 2 && tx < a.tile_x + 4;
-    const bool xr3 = colin && tx >= 3 && tx < a.tile_x + 3;
+    const bool colin = (uint32_t)gx < (uint32_t)nx;
+    const bool xr1 = colin && (uint32_t)(tx - 1) < (uint32_t)(a.tile_x + 4);
+    const bool xr2 = colin && (uint32_t)(tx - 2) < (uint32_t)(a.tile_x + 2);
+    const bool xr3 = colin && (uint32_t)(tx - 3) < (uint32_t)a.tile_x;
     // in-domain frame rows [ylo, yhi)
     const int ylo = kHalo - y0 > 0 ? kHalo - y0 : 0;
     const int yhi = ny - y0 + kHalo < FH ? ny - y0 + kHalo : FH;
@@ -242,7 +253,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     c.visc_mode = a.visc_mode;
     const T dt = T(a.dt);
     const T hdt = T(0.5 * a.dt);
-    const T rdt = T(1.0 / a.dt);
+    const T rdt = T(a.rdt);
     const T t = T(tnow);
     const T tp = T(tnow + a.dt);
     const T INF = M<T>::inf();
@@ -380,20 +391,20 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
             if (!(pold[k] > T(0) && p0[k] <= T(0))) tig[k] = INF;
     }
     {
-        const int fh = phase_copy(FH);
+        const int fh = phase_copy(a.tile_y) + 2 * kHalo, tw = phase_copy(ty), gxc = lane_copy(gx);
 #pragma unroll
         for (int k = 0; k < KR; k++) {
-            const int fy = ty + kNR * k;
+            const int fy = tw + kNR * k;
             if (fy < fh) A[fy][tx] = p0[k];
         }
     }
     __syncthreads();
     if (!interior) {
-        const int fh = phase_copy(FH);
+        const int fh = phase_copy(a.tile_y) + 2 * kHalo, tw = phase_copy(ty), gxc = lane_copy(gx);
 #pragma unroll
         for (int k = 0; k < KR; k++) {
-            const int fy = ty + kNR * k;
-            if (fy < fh) ghost_node(A, fy, tx, gx, y0 - kHalo + fy, nx, ny, false);
+            const int fy = tw + kNR * k;
+            if (fy < fh) ghost_node(A, fy, tx, gxc, y0 - kHalo + fy, nx, ny, false);
         }
         __syncthreads();
     }
@@ -407,9 +418,10 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     auto in1 = [&](int k) { return xr1 && k >= r1.k0 && k < r1.k1; };
     auto src1 = [&](int k) { return in1(k) ? idx0 + roff(k) : cbase; };
     Inputs<T> nxt = load_inputs<SMALL>(src1(0), cat, uw, vw, dzdx, dzdy);
+    const int ty1 = phase_copy(ty);
 #pragma unroll
     for (int k = 0; k < KR; k++) {
-        const int fy = ty + kNR * k;
+        const int fy = ty1 + kNR * k;
         const Inputs<T> cur = nxt;
         if (k + 1 < KR) nxt = load_inputs<SMALL>(src1(k + 1), cat, uw, vw, dzdx, dzdy);
         if (in1(k)) {
@@ -420,12 +432,13 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     }
     __syncthreads();
     if (!interior) {
-        const int fhb = phase_copy(FH - 1);
+        const int fhb = phase_copy(a.tile_y) + 2 * kHalo - 1, tw = phase_copy(ty);
+        const int gxc = lane_copy(gx);
 #pragma unroll
         for (int k = 0; k < KR; k++) {
-            const int fy = ty + kNR * k;
+            const int fy = tw + kNR * k;
             if (fy >= 1 && fy < fhb)
-                ghost_node(B, fy - 1, tx, gx, y0 - kHalo + fy, nx, ny, false);
+                ghost_node(B, fy - 1, tx, gxc, y0 - kHalo + fy, nx, ny, false);
         }
         __syncthreads();
     }
@@ -449,9 +462,10 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     auto src3 = [&](int k) { return in3(k) ? idx0 + roff(k) : cbase; };
     T fo1 = T(1);
     if (!REC) fo1 = at<SMALL>(frac, src3(0));
+    const int ty2 = phase_copy(ty);
 #pragma unroll
     for (int k = 0; k < KR; k++) {
-        const int fy = ty + kNR * k;
+        const int fy = ty2 + kNR * k;
         const Inputs<T> cur = nxt;
         const T fo = fo1;
         if (k + 1 < KR) {
@@ -528,14 +542,14 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     }
     if (!interior) {
         // ghost psi re-extrapolated, corners included; ghost t^ = t' (R19)
-        const int fh = phase_copy(FH);
+        const int fh = phase_copy(a.tile_y) + 2 * kHalo, tw = phase_copy(ty), gxc = lane_copy(gx);
 #pragma unroll
         for (int k = 0; k < KR; k++) {
-            const int fy = ty + kNR * k;
+            const int fy = tw + kNR * k;
             const int gy = y0 - kHalo + fy;
             if (fy < fh) {
-                ghost_node(A, fy, tx, gx, gy, nx, ny, true);
-                if (!(colin && gy >= 0 && gy < ny) && fy >= 2 && fy < fh - 2)
+                ghost_node(A, fy, tx, gxc, gy, nx, ny, true);
+                if (!((uint32_t)gxc < (uint32_t)nx && gy >= 0 && gy < ny) && fy >= 2 && fy < fh - 2)
                     C[fy - 2][tx] = tp;
             }
         }
@@ -552,9 +566,10 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     auto src4 = [&](int k) { return in4(k) ? idx0 + roff(k) : cbase; };
     // F of row k + 1 is loaded while row k computes
     T fo_next = at<SMALL>(frac, src4(0));
+    const int ty4 = phase_copy(ty);
 #pragma unroll
     for (int k = 0; k < KR; k++) {
-        const int fy = ty + kNR * k;
+        const int fy = ty4 + kNR * k;
         T fs = T(0);
         fl[k] = T(0);
         const T fo = fo_next;
@@ -587,16 +602,16 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     // ---- step 6: mean flux over each atmosphere cell of the tile, summed
     // in a fixed order (columns, then the column sums)
     {
-        const int fh = phase_copy(FH);
+        const int fh = phase_copy(a.tile_y) + 2 * kHalo, tw = phase_copy(ty), gxc = lane_copy(gx);
 #pragma unroll
         for (int k = 0; k < KR; k++) {
-            const int fy = ty + kNR * k;
+            const int fy = tw + kNR * k;
             if (fy < fh) A[fy][tx] = fl[k];
         }
     }
     __syncthreads();
     const int nI = a.tile_x / a.sr_x, nJ = a.tile_y / a.sr_y;
-    if (tx >= kHalo && tx < a.tile_x + kHalo) {
+    if ((uint32_t)(lane_copy(tx) - kHalo) < (uint32_t)phase_copy(a.tile_x)) {
         for (int J = ty; J < nJ; J += kNR) {
             const int r0 = kHalo + J * a.sr_y;
             T s1 = T(0), s2 = T(0);

@@ -102,7 +102,7 @@ __device__ __forceinline__ void small_tile(const StepArgs &a, const SmallPtrs<T>
     c.eps = T(a.eps);
     c.cap = T(a.ros_cap);
     c.visc_mode = a.visc_mode;
-    const T dt = T(a.dt), hdt = T(0.5 * a.dt), rdt = T(1.0 / a.dt);
+    const T dt = T(a.dt), hdt = T(0.5 * a.dt), rdt = T(a.rdt);
     const T t = T(tnow), tp = T(tnow + a.dt);
     const T INF = M<T>::inf();
 
