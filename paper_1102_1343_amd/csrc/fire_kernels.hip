@@ -240,10 +240,12 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     for (int i = tid; i < a.ncat; i += kBlock)
         make_row(coef + i * kNCoef, tab + i * kLRow, T(a.ros_cap));
     // set where a node of the tile or its ring burns or a cell of the tile has
-    // lost fuel
-    __shared__ int active;
+    // lost fuel; behind the table, where it takes 4 bytes of LDS (among the
+    // static arrays it takes 32, and a CU then holds three FP32 120 x 20
+    // work-groups instead of four at 21 fuels)
+    int *active = reinterpret_cast<int *>(tab + a.ncat * kLRow);
     constexpr int kStActive = 1 << 30;   // the same in a thread's status
-    if (!REC && tid == 0) active = 0;
+    if (!REC && tid == 0) *active = 0;
 
     Consts<T> c;
     c.rdx = T(a.rdx);
@@ -515,7 +517,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     }
     // a replay for the reverse pass needs psi only: no fuel fraction or flux
     if (REC) return;
-    if (st & kStActive) active = 1;
+    if (st & kStActive) *active = 1;
     st &= ~kStActive;
     __syncthreads();
     // No node of the tile and its ring has psi < 0 (a ghost is never below its
@@ -527,7 +529,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     // with fires and ignitions), 1501x1307 FP64 100 -> 90, 2048^2 FP32 42 -> 40.6;
     // where tiles burn the test costs a load of F (4099x4001 FP32, fires
     // throughout, 183 us before and after).
-    if (!active) {
+    if (!*active) {
         const int nI = phase_copy(a.tile_x) / a.sr_x, nJ = a.tile_y / a.sr_y;
         const int I0 = x0 / a.sr_x, J0 = y0 / a.sr_y;
         for (int q = tid; q < nI * nJ; q += kBlock) {
@@ -1012,9 +1014,14 @@ template <typename T> hipError_t ens_geo(const StepArgs &a, const StepBuffers &b
     return hipGetLastError();
 }
 
+// Dynamic LDS of a step work-group: the fuel table and the activity word.
+template <typename T> size_t step_lds(int ncat) {
+    return (size_t)ncat * kLRow * sizeof(T) + sizeof(int);
+}
+
 template <typename T, int KR, bool SMALL>
 hipError_t launch_one(const StepArgs &a, const StepBuffers &b, hipStream_t s) {
-    const size_t dyn = (size_t)a.ncat * kLRow * sizeof(T);
+    const size_t dyn = step_lds<T>(a.ncat);
     const int grid = a.per_xcd * 8;
     // the ignition geometry of the step: every step of an ensemble (its time
     // is on the device), a single domain's only while an ignition is active
@@ -1096,7 +1103,7 @@ hipError_t step_t(const StepArgs &a, const StepBuffers &b, hipStream_t s) {
 // XCD bands; 0 if the query fails).
 template <typename T, int KR>
 int persist_slots_k(int ncat, size_t ncells) {
-    const size_t dyn = (size_t)ncat * kLRow * sizeof(T);
+    const size_t dyn = step_lds<T>(ncat);
     const bool small = (uint64_t)ncells * sizeof(T) < ((uint64_t)1 << 32);
     int nb = 0, dev = 0, ncu = 0;
     const void *fn = small ? (const void *)k_ens_persist<T, KR, true>

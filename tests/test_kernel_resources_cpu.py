@@ -66,3 +66,12 @@ def test_default_step_has_registers_for_four_work_groups(kernels):
     assert k["vgpr_count"] <= 62
     assert k["vgpr_spill_count"] == 0 and k["private_segment_fixed_size"] == 0
     assert k["sgpr_spill_count"] <= 12
+
+
+@pytest.mark.parametrize("name,groups,row", [("k_stepIfLi7ELb1ELb0EE", 4, 48),
+                                             ("k_stepIdLi7ELb1ELb0EE", 2, 96)])
+def test_step_lds_with_21_fuels(kernels, name, groups, row):
+    """A CU's 160 KiB hold four FP32 (two FP64) 120 x 20 work-groups with the
+    rows of 21 fuels and the activity word behind the frames."""
+    k = _one(kernels, name)
+    assert groups * (k["group_segment_fixed_size"] + 21 * row + 4) <= 160 * 1024
