@@ -105,6 +105,7 @@ struct Rows {
     int k0, k1;
 };
 __device__ __forceinline__ Rows phase_rows(int ty, int lo, int hi) {
+    static_assert(kNR == 4, "row strides of a thread");
     const int t = phase_copy(ty);
     return {(lo - t + kNR - 1) >> 2, (hi - t + kNR - 1) >> 2};
 }
@@ -187,7 +188,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     // its own: shared between the phases, they do not fit the scalar registers
     // of 8 waves per SIMD (30 spills in the FP32 120 x 20 kernel, two to four
     // reloads from vector lanes in every row of the edge tiles' passes and of
-    // stage 2; with the copies 11, outside the row loops, 60 vector registers).
+    // stage 2; with the copies 9, outside the row loops, 63 vector registers).
     // Per step, vector row -> scalar row -> copies: 8192^2 556 -> 520 -> 517 us,
     // 4099x4001 with fires 181 -> 179 -> 176 us, 2048^2 41.4 -> 39.2 -> 37.8 us.
     const int ty = __builtin_amdgcn_readfirstlane(tyv);
@@ -458,18 +459,19 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     // F^n of row k + 1 at the tile's own cells, loaded with its inputs (loaded
     // and tested in the same row, the test also waits for the next row's
     // inputs: 4099x4001 with fires 179 -> 175 us a step, 700^2 FP32 19.9 ->
-    // 19.3).  A ring cell's F belongs to another work-group, which may be
+    // 19.3) and kept: loaded again in the fuel phase, a step of 4099x4001 with
+    // fires takes 175 us instead of 171.  A ring cell's F belongs to another work-group, which may be
     // writing it; it matters to neither F nor the fluxes here.
     auto in3 = [&](int k) { return xr3 && k >= r3.k0 && k < r3.k1; };
     auto src3 = [&](int k) { return in3(k) ? idx0 + roff(k) : cbase; };
-    T fo1 = T(1);
+    T fo1 = T(1), fk[KR];   // fk: for the fuel phase
     if (!REC) fo1 = at<SMALL>(frac, src3(0));
     const int ty2 = phase_copy(ty);
 #pragma unroll
     for (int k = 0; k < KR; k++) {
         const int fy = ty2 + kNR * k;
         const Inputs<T> cur = nxt;
-        const T fo = fo1;
+        const T fo = fk[k] = fo1;
         if (k + 1 < KR) {
             nxt = load_inputs<SMALL>(src2(k + 1), cat, uw, vw, dzdx, dzdy);
             if (!REC) fo1 = at<SMALL>(frac, src3(k + 1));
@@ -527,8 +529,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     // the flux frames and their sums, with four barriers, are LDS work that the
     // memory waits do not hide: per step 8192^2 FP32 572 -> 541 us (20 steps
     // with fires and ignitions), 1501x1307 FP64 100 -> 90, 2048^2 FP32 42 -> 40.6;
-    // where tiles burn the test costs a load of F (4099x4001 FP32, fires
-    // throughout, 183 us before and after).
+    // where tiles burn it costs the test alone.
     if (!*active) {
         const int nI = phase_copy(a.tile_x) / a.sr_x, nJ = a.tile_y / a.sr_y;
         const int I0 = x0 / a.sr_x, J0 = y0 / a.sr_y;
@@ -565,17 +566,13 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     T fl[KR];
     const Rows r4 = phase_rows(ty, lo3, hi3);
     auto in4 = [&](int k) { return xr3 && k >= r4.k0 && k < r4.k1; };
-    auto src4 = [&](int k) { return in4(k) ? idx0 + roff(k) : cbase; };
-    // F of row k + 1 is loaded while row k computes
-    T fo_next = at<SMALL>(frac, src4(0));
     const int ty4 = phase_copy(ty);
 #pragma unroll
     for (int k = 0; k < KR; k++) {
         const int fy = ty4 + kNR * k;
         T fs = T(0);
         fl[k] = T(0);
-        const T fo = fo_next;
-        if (k + 1 < KR) fo_next = at<SMALL>(frac, src4(k + 1));
+        const T fo = fk[k];
         if (in4(k)) {
             const uint32_t idx = idx0 + roff(k);
             T mn = vmin(vmin(A[fy - 1][tx - 1], A[fy - 1][tx]), A[fy - 1][tx + 1]);
