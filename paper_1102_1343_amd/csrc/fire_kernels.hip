@@ -99,14 +99,13 @@ __device__ __forceinline__ int lane_copy(int v) {
     return v;
 }
 
-// Rows k in [k0, k1) of a wave (frame rows ty + kNR k) that lie in the frame
+// Rows k in [k0, k1) of a wave (frame rows t + kNR k) that lie in the frame
 // rows [lo, hi).
 struct Rows {
     int k0, k1;
 };
-__device__ __forceinline__ Rows phase_rows(int ty, int lo, int hi) {
+__device__ __forceinline__ Rows phase_rows(int t, int lo, int hi) {
     static_assert(kNR == 4, "row strides of a thread");
-    const int t = phase_copy(ty);
     return {(lo - t + kNR - 1) >> 2, (hi - t + kNR - 1) >> 2};
 }
 
@@ -171,7 +170,8 @@ __device__ __forceinline__ T cell_fraction(const T (*A)[kFW], int fy, const T (*
 // work-groups fit in a CU's 160 KiB.
 // PRE: the per-tile ignition set-up comes from iuse / ilb / irow (a single
 // domain's step); otherwise it is formed here from the geometry table.
-template <typename T, int KR, bool SMALL, bool REC, bool PRE>
+// SROW: the wave's frame row is held in a scalar register (see below).
+template <typename T, int KR, bool SMALL, bool REC, bool PRE, bool SROW>
 __device__ __forceinline__ void
 step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const uint32_t cbase,
           const double tnow,
@@ -182,8 +182,11 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
           int32_t *mark, const uint32_t *__restrict__ iuse, const T *__restrict__ ilb,
           const T *__restrict__ irow) {
     // A wave's 64 lanes share one frame row: in a scalar register, the row's
-    // range tests and LDS row offsets cost no vector work, which is what this
-    // kernel is short of (84 % of the cycles of an unburnt 8192^2 step).  Each
+    // range tests and LDS row offsets cost no vector work, which is what the
+    // plain step is short of where it fills the chip (84 % of the cycles of an
+    // unburnt 8192^2 step), but they lengthen the chain of a wave, which is the
+    // time where it does not, and of the ensembles (step_rows() has the rule).
+    // Each
     // phase forms them, and the masks of the lanes' columns, from copies of
     // its own: shared between the phases, they do not fit the scalar registers
     // of 8 waves per SIMD (30 spills in the FP32 120 x 20 kernel, two to four
@@ -191,7 +194,8 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     // stage 2; with the copies 9, outside the row loops, 63 vector registers).
     // Per step, vector row -> scalar row -> copies: 8192^2 556 -> 520 -> 517 us,
     // 4099x4001 with fires 181 -> 179 -> 176 us, 2048^2 41.4 -> 39.2 -> 37.8 us.
-    const int ty = __builtin_amdgcn_readfirstlane(tyv);
+    const int ty = SROW ? __builtin_amdgcn_readfirstlane(tyv) : tyv;
+    auto row_copy = [](int v) { return SROW ? phase_copy(v) : lane_copy(v); };
     constexpr int FHM = kNR * KR;
     __shared__ T A[FHM][kFW];
     __shared__ T B[FHM - 2][kFW];
@@ -394,7 +398,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
             if (!(pold[k] > T(0) && p0[k] <= T(0))) tig[k] = INF;
     }
     {
-        const int fh = phase_copy(a.tile_y) + 2 * kHalo, tw = phase_copy(ty), gxc = lane_copy(gx);
+        const int fh = phase_copy(a.tile_y) + 2 * kHalo, tw = row_copy(ty), gxc = lane_copy(gx);
 #pragma unroll
         for (int k = 0; k < KR; k++) {
             const int fy = tw + kNR * k;
@@ -403,7 +407,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     }
     __syncthreads();
     if (!interior) {
-        const int fh = phase_copy(a.tile_y) + 2 * kHalo, tw = phase_copy(ty), gxc = lane_copy(gx);
+        const int fh = phase_copy(a.tile_y) + 2 * kHalo, tw = row_copy(ty), gxc = lane_copy(gx);
 #pragma unroll
         for (int k = 0; k < KR; k++) {
             const int fy = tw + kNR * k;
@@ -417,11 +421,11 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     // the per-cell inputs of row k + 1 are loaded while row k computes
     // (rows outside the stage load the domain's first cell instead, unused:
     // unconditional loads need no register copies)
-    const Rows r1 = phase_rows(ty, lo1, hi1);
+    const Rows r1 = phase_rows(row_copy(ty), lo1, hi1);
     auto in1 = [&](int k) { return xr1 && k >= r1.k0 && k < r1.k1; };
     auto src1 = [&](int k) { return in1(k) ? idx0 + roff(k) : cbase; };
     Inputs<T> nxt = load_inputs<SMALL>(src1(0), cat, uw, vw, dzdx, dzdy);
-    const int ty1 = phase_copy(ty);
+    const int ty1 = row_copy(ty);
 #pragma unroll
     for (int k = 0; k < KR; k++) {
         const int fy = ty1 + kNR * k;
@@ -435,7 +439,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     }
     __syncthreads();
     if (!interior) {
-        const int fhb = phase_copy(a.tile_y) + 2 * kHalo - 1, tw = phase_copy(ty);
+        const int fhb = phase_copy(a.tile_y) + 2 * kHalo - 1, tw = row_copy(ty);
         const int gxc = lane_copy(gx);
 #pragma unroll
         for (int k = 0; k < KR; k++) {
@@ -452,7 +456,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     // node times t^ = t' where psi^{n+1} >= 0, else t_i (Eq. 17)
     int st = 0;
     const int gw = a.guard;
-    const Rows r2 = phase_rows(ty, lo2, hi2), r3 = phase_rows(ty, lo3, hi3);
+    const Rows r2 = phase_rows(row_copy(ty), lo2, hi2), r3 = phase_rows(row_copy(ty), lo3, hi3);
     auto in2 = [&](int k) { return xr2 && k >= r2.k0 && k < r2.k1; };
     auto src2 = [&](int k) { return in2(k) ? idx0 + roff(k) : cbase; };
     nxt = load_inputs<SMALL>(src2(0), cat, uw, vw, dzdx, dzdy);
@@ -466,7 +470,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     auto src3 = [&](int k) { return in3(k) ? idx0 + roff(k) : cbase; };
     T fo1 = T(1), fk[KR];   // fk: for the fuel phase
     if (!REC) fo1 = at<SMALL>(frac, src3(0));
-    const int ty2 = phase_copy(ty);
+    const int ty2 = row_copy(ty);
 #pragma unroll
     for (int k = 0; k < KR; k++) {
         const int fy = ty2 + kNR * k;
@@ -545,7 +549,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     }
     if (!interior) {
         // ghost psi re-extrapolated, corners included; ghost t^ = t' (R19)
-        const int fh = phase_copy(a.tile_y) + 2 * kHalo, tw = phase_copy(ty), gxc = lane_copy(gx);
+        const int fh = phase_copy(a.tile_y) + 2 * kHalo, tw = row_copy(ty), gxc = lane_copy(gx);
 #pragma unroll
         for (int k = 0; k < KR; k++) {
             const int fy = tw + kNR * k;
@@ -564,9 +568,9 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     // burning sub-cell point: beta = 0 in every sub-cell and F = 1 exactly.
     // The sensible flux goes straight to B (not read in this phase).
     T fl[KR];
-    const Rows r4 = phase_rows(ty, lo3, hi3);
+    const Rows r4 = phase_rows(row_copy(ty), lo3, hi3);
     auto in4 = [&](int k) { return xr3 && k >= r4.k0 && k < r4.k1; };
-    const int ty4 = phase_copy(ty);
+    const int ty4 = row_copy(ty);
 #pragma unroll
     for (int k = 0; k < KR; k++) {
         const int fy = ty4 + kNR * k;
@@ -601,7 +605,7 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
     // ---- step 6: mean flux over each atmosphere cell of the tile, summed
     // in a fixed order (columns, then the column sums)
     {
-        const int fh = phase_copy(a.tile_y) + 2 * kHalo, tw = phase_copy(ty), gxc = lane_copy(gx);
+        const int fh = phase_copy(a.tile_y) + 2 * kHalo, tw = row_copy(ty), gxc = lane_copy(gx);
 #pragma unroll
         for (int k = 0; k < KR; k++) {
             const int fy = tw + kNR * k;
@@ -659,8 +663,20 @@ template <typename T, int KR> constexpr int waves_per_simd() {
 // The plain step at that tile (no ignition scratch in LDS: its set-up comes
 // from k_ign_plain) needs under 40 KiB, so four work-groups fit per CU, i.e.
 // 8 waves per SIMD, within 64 VGPRs and the scalar registers of 8 waves.
-template <typename T, int KR> constexpr int step_waves() {
-    return (sizeof(T) == 4 && KR == 7) ? 8 : waves_per_simd<T, KR>();
+// FEW: no more tiles than the chip takes at three work-groups per CU.
+template <typename T, int KR, bool FEW> constexpr int step_waves() {
+    return (sizeof(T) == 4 && KR == 7 && !FEW) ? 8 : waves_per_simd<T, KR>();
+}
+// Where the frame row goes into a scalar register: the FP32 120 x 20 step of
+// more tiles than that, whose 64 vector registers leave no room for another
+// form, and FP64.  20 steps, us, vector / scalar row: FP32 880^2 (352 tiles)
+// 362 / 372, 960^2 with 40 % burning 469 / 514, 1150^2 (580 tiles) 434 / 445,
+// 2048^2 (1854 tiles) 781 / 770; 8 steps of FP32 ensembles: 96 members of 64 to
+// 110 a side 311 / 341, 256 of 256 to 1024 8366 / 8482; FP64, 40 of 300 to 500
+// 2467 / 2428.
+constexpr int kFewTiles = 3 * 256;
+template <typename T, bool PLAIN, bool FEW> constexpr bool step_rows() {
+    return sizeof(T) == 8 || (PLAIN && !FEW);
 }
 
 // REC: the replay of a recorded run for its reverse pass.  Writes psi^{n+1},
@@ -670,8 +686,8 @@ template <typename T, int KR> constexpr int step_waves() {
 // every node whose ignition time this step sets.  The ignition set-up of
 // the tiles comes from k_ign_plain (iuse, ilb, irow; read only while an
 // ignition is active).
-template <typename T, int KR, bool SMALL, bool REC>
-__global__ void __launch_bounds__(kBlock, (step_waves<T, KR>()))
+template <typename T, int KR, bool SMALL, bool REC, bool FEW>
+__global__ void __launch_bounds__(kBlock, (step_waves<T, KR, FEW>()))
 k_step(const StepArgs a, const IgnTable<T> *itab, const T *__restrict__ psi_in,
        T *__restrict__ psi_out, T *tign, T *frac, const T *__restrict__ uw,
        const T *__restrict__ vw, const T *__restrict__ dzdx, const T *__restrict__ dzdy,
@@ -682,10 +698,9 @@ k_step(const StepArgs a, const IgnTable<T> *itab, const T *__restrict__ psi_in,
     const int bid = blockIdx.x;
     const int tile = (bid & 7) * a.per_xcd + (bid >> 3);
     if (tile >= a.ntiles) return;
-    step_tile<T, KR, SMALL, REC, true>(a, tile, threadIdx.x, threadIdx.y, 0u, a.t, itab, psi_in,
-                                       psi_out, tign, frac, uw, vw,
-                                       dzdx, dzdy, cat, coef, fsens, flat, status, rec_p0, rec_b,
-                                       mark, iuse, ilb, irow);
+    step_tile<T, KR, SMALL, REC, true, step_rows<T, true, FEW>()>(
+        a, tile, threadIdx.x, threadIdx.y, 0u, a.t, itab, psi_in, psi_out, tign, frac, uw, vw,
+        dzdx, dzdy, cat, coef, fsens, flat, status, rec_p0, rec_b, mark, iuse, ilb, irow);
 }
 
 // An ensemble of domains in one launch: the tiles of all domains form one
@@ -734,14 +749,14 @@ ens_tile(const StepArgs &common, const int g, const int tx, const int ty,
     if (SMALL) {
         // the member's first element goes into the 32-bit element index, so
         // the array bases stay the launch's (no per-member 64-bit pointers)
-        step_tile<T, KR, SMALL, false, false>(a, g - d.tile0, tx, ty, (uint32_t)d.cell_off,
+        step_tile<T, KR, SMALL, false, false, step_rows<T, false, false>()>(a, g - d.tile0, tx, ty, (uint32_t)d.cell_off,
                                               tnow, itab, pin,
                                               pout, tign, frac, uw, vw, dzdx, dzdy, cat, coef,
                                               fsens + a0, flat + a0, status + di, nullptr,
                                               nullptr, nullptr, nullptr, nullptr, nullptr);
     } else {
         const size_t c0 = (size_t)d.cell_off;
-        step_tile<T, KR, SMALL, false, false>(a, g - d.tile0, tx, ty, 0u, tnow, itab, pin + c0,
+        step_tile<T, KR, SMALL, false, false, step_rows<T, false, false>()>(a, g - d.tile0, tx, ty, 0u, tnow, itab, pin + c0,
                                               pout + c0,
                                               tign + c0, frac + c0, uw + c0, vw + c0, dzdx + c0,
                                               dzdy + c0, cat + c0, coef, fsens + a0, flat + a0,
@@ -1020,6 +1035,8 @@ template <typename T, int KR, bool SMALL>
 hipError_t launch_one(const StepArgs &a, const StepBuffers &b, hipStream_t s) {
     const size_t dyn = step_lds<T>(a.ncat);
     const int grid = a.per_xcd * 8;
+    constexpr bool kMayFew = sizeof(T) == 4 && KR == 7 && SMALL;
+    const bool few = kMayFew && a.ntiles <= kFewTiles;
     // the ignition geometry of the step: every step of an ensemble (its time
     // is on the device), a single domain's only while an ignition is active
     const char *iset = (const char *)b.ign_set;
@@ -1053,14 +1070,16 @@ hipError_t launch_one(const StepArgs &a, const StepBuffers &b, hipStream_t s) {
                            (const T *)b.v, (const T *)b.dzdx, (const T *)b.dzdy, b.cat,
                            (const T *)b.coef, (T *)b.fsens, (T *)b.flat, b.status);
     } else if (b.rec_p0) {
-        hipLaunchKernelGGL((k_step<T, KR, SMALL, true>), dim3(grid), dim3(kFW, kNR), dyn, s, a,
+        auto *fn = few ? k_step<T, KR, SMALL, true, kMayFew> : k_step<T, KR, SMALL, true, false>;
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(kFW, kNR), dyn, s, a,
                            (const IgnTable<T> *)b.ign_tab, (const T *)b.psi_in, (T *)b.psi_out,
                            (T *)b.tign, (T *)b.frac, (const T *)b.u, (const T *)b.v,
                            (const T *)b.dzdx, (const T *)b.dzdy, b.cat, (const T *)b.coef,
                            (T *)b.fsens, (T *)b.flat, b.status, (T *)b.rec_p0, (T *)b.rec_b,
                            (int32_t *)nullptr, iuse, ilb, irow);
     } else {
-        hipLaunchKernelGGL((k_step<T, KR, SMALL, false>), dim3(grid), dim3(kFW, kNR), dyn, s, a,
+        auto *fn = few ? k_step<T, KR, SMALL, false, kMayFew> : k_step<T, KR, SMALL, false, false>;
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(kFW, kNR), dyn, s, a,
                            (const IgnTable<T> *)b.ign_tab, (const T *)b.psi_in, (T *)b.psi_out,
                            (T *)b.tign, (T *)b.frac, (const T *)b.u, (const T *)b.v,
                            (const T *)b.dzdx, (const T *)b.dzdy, b.cat, (const T *)b.coef,

@@ -62,16 +62,27 @@ def test_default_step_has_registers_for_four_work_groups(kernels):
     registers; nothing in scratch, and few scalar spills (values used once, in
     the ignition set-up and at the domain's edge: row numbers and masks that
     live across the kernel's phases give 28 and more)."""
-    k = _one(kernels, "k_stepIfLi7ELb1ELb0EE")
+    k = _one(kernels, "k_stepIfLi7ELb1ELb0ELb0EE")
     assert k["vgpr_count"] <= 64
     assert k["vgpr_spill_count"] == 0 and k["private_segment_fixed_size"] == 0
     assert k["sgpr_spill_count"] <= 12
 
 
-@pytest.mark.parametrize("name,groups,row", [("k_stepIfLi7ELb1ELb0EE", 4, 48),
-                                             ("k_stepIdLi7ELb1ELb0EE", 2, 96)])
+@pytest.mark.parametrize("name,groups,row", [("k_stepIfLi7ELb1ELb0ELb0EE", 4, 48),
+                                             ("k_stepIdLi7ELb1ELb0ELb0EE", 2, 96)])
 def test_step_lds_with_21_fuels(kernels, name, groups, row):
     """A CU's 160 KiB hold four FP32 (two FP64) 120 x 20 work-groups with the
     rows of 21 fuels and the activity word behind the frames."""
     k = _one(kernels, name)
     assert groups * (k["group_segment_fixed_size"] + 21 * row + 4) <= 160 * 1024
+
+
+@pytest.mark.parametrize("name", ["k_stepIfLi7ELb1ELb0ELb1EE", "k_ens_stepIfLi7ELb1EE"])
+def test_few_tiles_and_ensembles_have_registers_for_three_work_groups(kernels, name):
+    """FP32 120 x 20 tiles, three work-groups (24 waves) on a CU: at most 80
+    vector registers, no scratch, and the wave's row in a vector register, so
+    no scalar spills."""
+    k = _one(kernels, name)
+    assert k["vgpr_count"] <= 80
+    assert k["vgpr_spill_count"] == 0 and k["private_segment_fixed_size"] == 0
+    assert k["sgpr_spill_count"] == 0
