@@ -96,33 +96,76 @@ void ignition_window(const fire_ignition *ign, int n, double *lo, double *hi) {
 // mesh takes them up to 650 000: 660^2 12.4-15.0 / 18.9, 700^2 14.7-15.8 / 19.3
 // (17.0 / 24.4 while four lines grow), 780^2 16.4-17.1 / 19.1, 860^2 18.0-20.3 /
 // 21.7, 960^2 23.2-25.3 / 21.8.
-// The tile is the smallest of whole atmosphere cells, at least 8 cells a
-// side, that gives at most 700 work-groups (256 CUs, two or three each).
+//
+// The tile is of whole atmosphere cells, at least 8 cells a side, and never
+// larger than the largest member.  FP64 (84 vector registers: 20 waves on a
+// CU): the largest of four waves, of which five fit, or the smallest where that
+// has more.  FP32 (32 waves on a CU): grown by turns in x and y, the one with
+// the fewest waves on the busiest CU; with one node per thread if those are 18
+// or fewer, else also with two.  Us per step, the rule before (at most 700
+// work-groups, which counted on two or three FP64 ones per CU and which many
+// members or long strips never reach) / this: FP64 400^2 19.1 / 17.6, 500^2
+// 25.6 / 23.3 (refinement 4: 25.6 / 20.9), 600^2 31.2 / 30.0, 150 members of
+// 50^2 66.7 / 55.6; FP32 600^2 15.1 / 11.4, 700^2 15.6 / 13.4, 1000 members of
+// 20^2 52 / 41.
 StepKind step_kind(const fire_mesh *m, int ndom, int *tx, int *ty) {
     int64_t cells = 0;
-    for (int k = 0; k < ndom; k++) cells += (int64_t)m[k].nx * m[k].ny;
+    int mx = 0, my = 0;
+    for (int k = 0; k < ndom; k++) {
+        cells += (int64_t)m[k].nx * m[k].ny;
+        mx = m[k].nx > mx ? m[k].nx : mx;
+        my = m[k].ny > my ? m[k].ny : my;
+    }
+    const bool f32 = m->dtype == FIRE_F32;
+    if (cells > (ndom == 1 && f32 ? kSmallCells32 : kSmallCells)) return kTiled;
     const int sx = m->sr_x, sy = m->sr_y;
-    // nodes of a tile with its two inner rings: two per thread, and LDS of at
-    // most 64 KiB with 256 fuels
-    const int most = m->dtype == FIRE_F64 ? 1024 : 2048;
-    if (cells <= (ndom == 1 && m->dtype == FIRE_F32 ? kSmallCells32 : kSmallCells)) {
-        int x = (8 + sx - 1) / sx * sx, y = (8 + sy - 1) / sy * sy;
-        for (;;) {
-            int64_t n = 0;
-            for (int k = 0; k < ndom; k++)
-                n += (int64_t)((m[k].nx + x - 1) / x) * ((m[k].ny + y - 1) / y);
-            const int x1 = x < y ? x + sx : x, y1 = x < y ? y : y + sy;
-            if (n <= 700 || (x1 + 4) * (y1 + 4) > most) break;
-            x = x1;
-            y = y1;
-        }
-        if ((x + 4) * (y + 4) <= most) {
+    // nodes of a tile with its two inner rings: two per thread (FP64: one),
+    // and LDS of at most 64 KiB with 256 fuels
+    const int most = f32 ? 2048 : 1024;
+    auto nodes = [](int x, int y) { return (x + 4) * (y + 4); };
+    int x = (8 + sx - 1) / sx * sx, y = (8 + sy - 1) / sy * sy;
+    if (nodes(x, y) > most) return kTiled;
+    *tx = x;
+    *ty = y;
+    if (!f32) {
+        for (int v = y; nodes(x, v) <= 256 && v < my + sy; v += sy)
+            for (int u = x; nodes(u, v) <= 256 && u < mx + sx; u += sx)
+                if (nodes(u, v) > nodes(*tx, *ty)) {
+                    *tx = u;
+                    *ty = v;
+                }
+        return kSmall;
+    }
+    int64_t fewest = INT64_MAX, fewest1 = INT64_MAX;
+    int x1 = x, y1 = y;   // the best tile of one node per thread
+    for (;;) {
+        int npt, nt;
+        small_block(x, y, &npt, &nt);
+        int64_t n = 0;
+        for (int k = 0; k < ndom; k++)
+            n += (int64_t)((m[k].nx + x - 1) / x) * ((m[k].ny + y - 1) / y);
+        const int64_t w = (n + 255) / 256 * (nt / 64);
+        if (w < fewest) {
+            fewest = w;
             *tx = x;
             *ty = y;
-            return kSmall;
         }
+        if (npt == 1 && w < fewest1) {
+            fewest1 = w;
+            x1 = x;
+            y1 = y;
+        }
+        const bool gx = x < mx, gy = y < my;
+        if (gx && (x <= y || !gy)) x += sx;
+        else if (gy) y += sy;
+        else break;
+        if (nodes(x, y) > most) break;
     }
-    return kTiled;
+    if (fewest1 <= 18) {
+        *tx = x1;
+        *ty = y1;
+    }
+    return kSmall;
 }
 
 bool tile_ok(const fire_mesh *m, int tile_x, int tile_y) {
@@ -198,7 +241,11 @@ hipError_t step_raw(fire_ctx *c, const void *psi_in, void *psi_out, void *tign, 
     a.ny = m.ny;
     a.tile_x = c->tile_x;
     a.tile_y = c->tile_y;
-    const StepKind kind = c->tile_set ? kTiled : step_kind(&m, 1, &a.tile_x, &a.tile_y);
+    const int kind = c->tile_set ? (int)kTiled : c->kind;
+    if (kind == kSmall) {
+        a.tile_x = c->unit_x;
+        a.tile_y = c->unit_y;
+    }
     a.tiles_x = (m.nx + a.tile_x - 1) / a.tile_x;
     const int tiles_y = (m.ny + a.tile_y - 1) / a.tile_y;
     a.ntiles = a.tiles_x * tiles_y;
@@ -329,6 +376,7 @@ int fire_init(fire_ctx **out, const fire_mesh *mesh, const fire_fuel *cats, int3
     c->mark_step = 0;
     c->nstep = 0;
     c->tile_set = 0;
+    c->kind = step_kind(mesh, 1, &c->unit_x, &c->unit_y);
     default_tile(mesh, &c->tile_x, &c->tile_y);
     if (!tile_ok(mesh, c->tile_x, c->tile_y)) {
         delete c;

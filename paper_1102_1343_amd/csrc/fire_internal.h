@@ -160,6 +160,8 @@ struct fire_ctx {
     hipStream_t stream;
     int tile_x, tile_y;
     int tile_set;          // the tile shape was chosen by fire_set_tile
+    int kind;              // else: the step kernel (StepKind) and its small tile
+    int unit_x, unit_y;
     int stopped;           // FIRE_ERR_BOUNDARY / FIRE_ERR_NONFINITE once the stop
                            // policy has seen that status bit, else 0
     // Stop policy: after each step the status word is copied to pinned host

@@ -123,3 +123,18 @@ def test_largest_small_single_precision_mesh_and_the_next(nx, ny, sr_x, sr_y):
     for x, y in zip(a[:-1], b[:-1]):
         assert torch.equal(x, y)
     assert a[-1] == b[-1]
+
+
+# strips whose tiles grow along their length only (up to 130 x 10 and 10 x 130
+# nodes), two ratios with tiles of nearly four waves in FP64, the widest cells
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("nx,ny,sr_x,sr_y,tile",
+                         [(43011, 9, 10, 10, (120, 20)), (7, 50001, 10, 10, (120, 20)),
+                          (501, 333, 8, 5, (120, 20)), (333, 501, 5, 7, (120, 21)),
+                          (245, 83, 122, 7, (122, 21))])
+def test_small_tiles_of_every_proportion(nx, ny, sr_x, sr_y, tile, dtype):
+    prob = _problem(nx, ny, sr_x, sr_y)
+    a, b = _run(prob, dtype, None), _run(prob, dtype, tile)
+    for name, x, y in zip(("psi", "tign", "frac", "sens", "lat", "sens1", "lat1"), a, b):
+        assert torch.equal(x, y), name
+    assert a[-1] == b[-1]
