@@ -219,6 +219,8 @@ int fire_ros_eval(fire_ctx *ctx, const uint8_t *cat, const void *un, const void 
  * ignition at every node (same results, slower while ignitions are
  * active). */
 int fire_set_tile(fire_ctx *ctx, int32_t tile_x, int32_t tile_y);
+/* The tiled kernel's shape: the one set, or fire_default_tile()'s (a context
+ * of a small mesh whose shape was never set does not run it). */
 int fire_get_tile(fire_ctx *ctx, int32_t *tile_x, int32_t *tile_y);
 
 /* Change the stream later calls enqueue on. */
@@ -315,12 +317,12 @@ size_t fire_ens_tune_bytes(fire_ens *e);
 
 /*
  * Times reps steps for each candidate tile shape cand[2*i], cand[2*i+1]
- * (i < ncand) and for the kernel an ensemble without a set shape takes, with
- * the given inputs, keeps the fastest (the fastest candidate is written to
- * best[2]) and restores the state, time and status from a snapshot in the caller's
+ * (i < ncand) with the given inputs, keeps the fastest (written to best[2])
+ * and restores the state, time and status from a snapshot in the caller's
  * scratch (fire_ens_tune_bytes(), 256-byte aligned), so the ensemble is left
- * as before the call except for the tile shape.  The flux buffers are
- * overwritten.  Waits.
+ * as before the call except for the tile shape, which is then a set one (see
+ * fire_ens_set_tile()): an ensemble that is faster without, as small ones
+ * are, is better left untuned.  The flux buffers are overwritten.  Waits.
  */
 int fire_ens_autotune(fire_ens *e, const void *u, const void *v, double dt, void *flux_sens,
                       void *flux_lat, const int32_t *cand, int32_t ncand, int32_t reps,

@@ -425,17 +425,8 @@ int fire_ens_autotune(fire_ens *e, const void *u, const void *v, double dt, void
     }
     float best_ms = 0.0f;
     int best_i = -1, rc = FIRE_OK;
-    // the candidates, then (i == ncand) the kernel that is taken when no
-    // shape is set, where that is another one
-    bool own_best = false;
-    for (int i = 0; i <= ncand && rc == FIRE_OK; i++) {
-        if (i < ncand) {
-            rc = fire_ens_set_tile(e, cand[2 * i], cand[2 * i + 1]);
-        } else {
-            e->tile_set = 0;
-            rc = build_worklist(e);
-            if (rc == FIRE_OK && e->kind == kTiled) break;
-        }
+    for (int i = 0; i < ncand && rc == FIRE_OK; i++) {
+        rc = fire_ens_set_tile(e, cand[2 * i], cand[2 * i + 1]);
         if (rc != FIRE_OK) break;
         rc = fire_ens_step(e, u, v, dt, flux_sens, flux_lat);   // warm-up
         if (rc != FIRE_OK) break;
@@ -448,8 +439,7 @@ int fire_ens_autotune(fire_ens *e, const void *u, const void *v, double dt, void
         if (rc == FIRE_OK && hipEventElapsedTime(&ms, ev0, ev1) != hipSuccess) rc = FIRE_ERR_HIP;
         if (rc == FIRE_OK && (best_i < 0 || ms < best_ms)) {
             best_ms = ms;
-            if (i < ncand) best_i = i;
-            else own_best = true;
+            best_i = i;
         }
         // restore the snapshot into the buffer that is current again
         h = copy(ptr(e, e->off_psi[cur0]), sc + o_psi, n);
@@ -465,10 +455,6 @@ int fire_ens_autotune(fire_ens *e, const void *u, const void *v, double dt, void
     best[0] = cand[2 * best_i];
     best[1] = cand[2 * best_i + 1];
     rc = fire_ens_set_tile(e, best[0], best[1]);
-    if (rc == FIRE_OK && own_best) {
-        e->tile_set = 0;
-        rc = build_worklist(e);
-    }
     if (rc == FIRE_OK && hipStreamSynchronize(e->stream) != hipSuccess) rc = FIRE_ERR_HIP;
     return rc;
 }

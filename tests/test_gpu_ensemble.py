@@ -243,3 +243,29 @@ def test_ensemble256_members_bitwise_after_500_steps():
         assert abs(ens.t - ref[0][6]) == 0.0
         del graph
         ens.close()
+
+
+def _kernels_of(call):
+    """Names of the kernels that a call launches."""
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [e.name for e in prof.events()]
+
+
+def test_autotuned_shape_is_the_one_that_runs():
+    """A small ensemble without a set shape takes the small tiles; the shape
+    that autotune returns, and get_tile reports, is what runs afterwards."""
+    probs = _members(4, 40, 90, 909, torch.float32)
+    ens = F.FireEnsemble.from_problems(probs, dtype=torch.float32)
+    u, v = _ens_wind(ens, probs)
+    fs, fl = ens.new_flux()
+    step = lambda: ens.step(u, v, probs[0].dt, fs, fl)   # noqa: E731
+    step()
+    if not any("k_ens_small" in n for n in _kernels_of(step)):
+        pytest.skip("no kernel names from the profiler")
+    best = ens.autotune(u, v, probs[0].dt, [(120, 20), (60, 20)], reps=2)
+    assert ens.get_tile() == best
+    names = _kernels_of(step)
+    assert any("k_ens_step" in n for n in names) and not any("k_ens_small" in n for n in names)
