@@ -15,9 +15,11 @@ import pytest
 import torch
 
 from paper_1102_1343_amd import fire as F
+from paper_1102_1343_amd import synth
 
-from adjoint_ref import Case
+from adjoint_ref import Case, run_F
 from parity import host
+from test_gpu_small import _problem
 
 pytestmark = pytest.mark.gpu
 
@@ -162,3 +164,76 @@ def test_adjoint_every_cell_against_oracle_fd():
              f"nonzero cells {np.count_nonzero(np.abs(ref) > 1e-6 * scale)}")
         assert np.count_nonzero(np.abs(ref) > 1e-3 * scale) >= 20
         assert err.max() <= 1e-5 * scale
+
+
+class _EdgeCase(Case):
+    """A ragged adjoint case with its fires at the mesh's edge and corner."""
+
+    def __init__(self, nx, ny, nsteps, seed):
+        prob, pert = synth.adjoint_case(n=max(nx, ny), steps=nsteps, seed=seed)
+        crop = lambda a: np.ascontiguousarray(a[:ny, :nx])   # noqa: E731
+        W, H = nx * prob.dx, ny * prob.dy
+        at = ((0.5 * prob.dx, 0.45 * H), (W - 2.2 * prob.dx, H - 1.7 * prob.dy))
+        ign = [dict(g, ax=x, ay=y, bx=x, by=y) for g, (x, y) in zip(prob.ignitions, at)]
+        self.prob = synth.Problem(nx, ny, prob.dx, prob.dy, prob.sr_x, prob.sr_y, prob.fuels,
+                                  crop(prob.cat), crop(prob.dzdx), crop(prob.dzdy), ign, prob.dt,
+                                  nsteps, [tuple(crop(a) for a in prob.wind[0])], 0,
+                                  dict(prob.params), prob.name)
+        self.nsteps = nsteps
+        self.u, self.v = self.prob.wind[0]
+        self.mult = np.ones(len(prob.fuels))
+        self.shift = np.zeros((len(ign), 2))
+        s = pert["wind_scale"]
+        self.target = run_F(self.prob, s * self.u, s * self.v, pert["mult"], pert["shift"], nsteps)
+
+
+@pytest.mark.parametrize("nx,ny,nsteps", [(97, 51, 60), (33, 130, 50), (485, 301, 40)])
+def test_adjoint_of_ragged_meshes_with_fire_at_the_edge(nx, ny, nsteps):
+    """Several 32 x 16 reverse tiles with remainders (304 of them in the last
+    case), the live ones at the edges, against the oracle's differences."""
+    case = _EdgeCase(nx, ny, nsteps, seed=5)
+    gu, gv, gm, gs, Fend = _gpu_grads(case, torch.float64, every=17)
+    assert (Fend[:, 0] < 1).any() and (Fend[-1, :] < 1).any() and (Fend[:, -1] < 1).any()
+    k = int(np.argmax(np.abs(gm)))
+    _close([gm[k]], [case.fd_mult(k)], 1e-5, f"dL/dm_{k}")
+    _close([gs[1, 0], gs[1, 1]], [case.fd_shift(1, 0), case.fd_shift(1, 1)], 1e-5, "dL/dshift")
+    rng = np.random.default_rng(9)
+    du, dv = rng.normal(size=case.u.shape), rng.normal(size=case.v.shape)
+    _close([float(np.sum(gu * du) + np.sum(gv * dv))], [case.fd_wind(du, dv)], 1e-5,
+           "dL/d(u,v) direction")
+
+
+def _grads_with(prob, dtype, nsteps, every, tile):
+    fire = F.Fire.from_problem(prob, dtype=dtype)
+    if tile:
+        fire.set_tile(*tile)
+    adj = F.FireAdjoint(fire, nsteps, every)
+    u, v = (torch.from_numpy(a).to("cuda", dtype).contiguous() for a in prob.wind[0])
+    Fend = adj.forward(u, v, prob.dt).clone()
+    w = torch.from_numpy(np.random.default_rng(4).normal(size=u.shape)).to("cuda", dtype)
+    gu, gv, gm, gs = adj.backward(w.contiguous())
+    torch.cuda.synchronize()
+    out = [host(Fend), host(gu), host(gv), gm.copy(), gs.copy()]
+    adj.close()
+    fire.close()
+    return out
+
+
+@pytest.mark.parametrize("nx,ny,dtype,tile", [
+    (131, 77, torch.float32, (120, 20)), (131, 77, torch.float64, (120, 20)),
+    (331, 257, torch.float32, (120, 20)), (331, 257, torch.float64, (60, 10)),
+    (961, 780, torch.float32, (60, 10)), (1441, 1281, torch.float32, (60, 40))])
+def test_gradients_do_not_depend_on_the_step_kernel(nx, ny, dtype, tile):
+    """Recording forward and replay in the kernel a context takes without a
+    set shape (small tiles; the last two meshes: the tiled kernel of few and of
+    many tiles)
+    and in the tiled kernel of another shape: the same gradients bit for bit,
+    at several checkpoint intervals."""
+    nsteps = 12
+    prob = _problem(nx, ny, 10, 10)
+    ref = _grads_with(prob, dtype, nsteps, nsteps, None)
+    assert np.count_nonzero(ref[1]) > 50 and np.count_nonzero(ref[4]) > 0
+    for every in (5, nsteps):
+        got = _grads_with(prob, dtype, nsteps, every, tile)
+        for name, a, b in zip(("F", "du", "dv", "dmult", "dshift"), got, ref):
+            assert np.array_equal(a, b), (name, every)
