@@ -55,7 +55,8 @@ __device__ __forceinline__ int ext_idx(const AdjArgs &a, int x, int y) {
     return (y + 1) * (a.nx + 2) + (x + 1);
 }
 
-// The reverse step works on tiles of kRTX x kRTY nodes (one work-group of
+// The reverse step works on tiles of kRTX x kRTY nodes, one work-group each
+// (k_rev_tile: kRT threads, one per node of the tile and its ring; k_rev_part1:
 // kAB threads, two nodes each).  Per-tile flags record where an array may be
 // nonzero: dL/dpsi^{n+1} (two buffers, l1[0] / l1[1]), the crossing part of
 // dL/dpsi' (lp0) and dL/dt_i (lt).  The adjoint of a run is nonzero only
@@ -70,20 +71,6 @@ struct AdjFlags {
 
 __device__ __forceinline__ int rtiles_x(const AdjArgs &a) { return (a.nx + kRTX - 1) / kRTX; }
 __device__ __forceinline__ int rtiles_y(const AdjArgs &a) { return (a.ny + kRTY - 1) / kRTY; }
-
-// Whether tile t or one of its eight neighbours has its flag set (the
-// reach of the ring's gathers, the ghost transposes included).
-__device__ __forceinline__ bool nbhd_flag(const int32_t *f, const AdjArgs &a, int t) {
-    const int tx = rtiles_x(a), ty = rtiles_y(a);
-    const int cx = t % tx, cy = t / tx;
-    bool any = false;
-    for (int dy = -1; dy <= 1; dy++)
-        for (int dx = -1; dx <= 1; dx++) {
-            const int x = cx + dx, y = cy + dy;
-            if (x >= 0 && x < tx && y >= 0 && y < ty && f[y * tx + x]) any = true;
-        }
-    return any;
-}
 
 // d ghost(p, q) / d(p, q): ghost = 2p - q when p >= q, else q.
 template <typename T> __device__ __forceinline__ void dghost(T p, T q, T &dp, T &dq) {

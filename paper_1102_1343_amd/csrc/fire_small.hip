@@ -40,8 +40,6 @@ template <typename T> struct SmallPtrs {
     int32_t *mark;
 };
 
-__device__ __forceinline__ bool any(bool c) { return __builtin_amdgcn_ballot_w64(c) != 0; }
-
 // One node of a thread: its place in the frame and in the domain, and what
 // the step reads there.
 template <typename T> struct Node {
@@ -401,10 +399,11 @@ hipError_t launch_t(const StepArgs &a, const StepBuffers &b, const fire_ignition
     small_block(a.tile_x, a.tile_y, &npt, &nt);
     const int F = (a.tile_x + 2 * kHalo) * (a.tile_y + 2 * kHalo);
     const size_t dyn = ((size_t)3 * F + a.ncat * kLRow + a.tile_x * a.tile_y) * sizeof(T) + 16;
-    if (F > (npt + 2) * nt) return hipErrorInvalidValue;
+    constexpr int kMost = sizeof(T) == 4 ? 2 : 1;   // nodes per thread (step_kind)
+    if (npt > kMost || F > (npt + 2) * nt) return hipErrorInvalidValue;
     const dim3 grid(a.ntiles), blk(nt);
     if (b.ens_doms) {
-        auto *fn = npt == 1 ? k_ens_small<T, 1> : k_ens_small<T, 2>;
+        auto *fn = npt == 1 ? k_ens_small<T, 1> : k_ens_small<T, kMost>;
         hipLaunchKernelGGL(fn, grid, blk, dyn, s, a, p, coef, b.ens_doms, b.ens_tile_dom,
                            b.ens_clock, (const char *)b.ign_tab, (T *)b.psi_in, (T *)b.psi_out);
         return hipGetLastError();
@@ -416,8 +415,8 @@ hipError_t launch_t(const StepArgs &a, const StepBuffers &b, const fire_ignition
         prm.tab.on[g] = g < a.nign && ign_setup<T>(ign[g], a.t, geo) ? 1 : 0;
         prm.tab.g[g] = geo;
     }
-    auto *fn = b.rec_p0 ? (npt == 1 ? k_step_small<T, true, 1> : k_step_small<T, true, 2>)
-                        : (npt == 1 ? k_step_small<T, false, 1> : k_step_small<T, false, 2>);
+    auto *fn = b.rec_p0 ? (npt == 1 ? k_step_small<T, true, 1> : k_step_small<T, true, kMost>)
+                        : (npt == 1 ? k_step_small<T, false, 1> : k_step_small<T, false, kMost>);
     hipLaunchKernelGGL(fn, grid, blk, dyn, s, prm, p, coef);
     return hipGetLastError();
 }

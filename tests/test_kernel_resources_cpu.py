@@ -86,3 +86,11 @@ def test_few_tiles_and_ensembles_have_registers_for_three_work_groups(kernels, n
     assert k["vgpr_count"] <= 80
     assert k["vgpr_spill_count"] == 0 and k["private_segment_fixed_size"] == 0
     assert k["sgpr_spill_count"] == 0
+
+
+def test_small_tile_kernels_that_no_rule_launches_are_not_built(kernels):
+    """FP64 small tiles have at most 1024 nodes, one per thread."""
+    small = [k for k in kernels if "k_step_small" in k or "k_ens_small" in k]
+    assert len(small) == 9
+    assert not [k for k in small if "smallIdLi2E" in k or "smallIdLb0ELi2E" in k
+                or "smallIdLb1ELi2E" in k]
