@@ -735,6 +735,10 @@ k_rev_part1(const AdjArgs a, int n, const int32_t *set_step, const T *psi_n, con
 // fuel table comes through LDS, so no load waits for another.  1024^2
 // FP32, 100 steps: 22 -> 14 us per reversed step (several tiles per
 // work-group, to spare the dead ones' launch: 15.7, live tiles then queue).
+// FP64 takes 133 registers, so one work-group of ten waves fits a CU, and from
+// 257 tiles on they run in rounds; still 362^2 (276 tiles) 19.2 -> 17.1 us, 500^2
+// 24.3 -> 20.8 (after 400 steps, with more of them live, 36.5 -> 34.1), 1000^2
+// 45.3 -> 38.5.
 template <typename T>
 __global__ void __launch_bounds__(kRT)
 k_rev_tile(const AdjArgs a2, const AdjArgs a1, int part1, int n1, const T *Di, const T *L1i,

@@ -83,19 +83,20 @@ void ignition_window(const fire_ignition *ign, int n, double *lo, double *hi) {
     }
 }
 
-// Which step kernel a mesh (or an ensemble of ncells cells in all) takes when
+// Which step kernel a mesh (or an ensemble of ndom meshes) takes when
 // no tile shape was chosen, and the shape of a work-group's tile.
 //
 // Small tiles (fire_small.hip) where the mesh is too small to fill the GPU
 // with the 120 x 20 tiles of fire_kernels.hip: the step is then the latency of
-// one work-group, not throughput.  Measured, us per step small / tiled: 128^2
-// FP32 7.6 / 17, FP64 9.3 / 35; 300^2 8.6 / 17, 14 / 35; 600^2 14.6 / 17.8,
-// 32 / 36; 700^2 15.7-22.6 / 18-20, 39 / 39; 800^2 18-24 / 18-20, 47 / 47;
-// 1000^2 25 / 21, 65 / 51 (the rings computed twice and the waves' number
+// one work-group, not throughput.  Measured, us per step small / tiled, in
+// brackets while four lines grow: FP64 128^2 10.5 / 37.0 [10.7 / 42.1], 300^2
+// 13.4 / 40.5 [13.6 / 39.2], 500^2 23.3 / 33.6 [25.0 / 36.1], 632^2 32.8 / 37.5
+// [36.6 / 37.2], 700^2 37 / 38.6 [45 / 37.7] (beyond, the rings computed twice
 // cost more than the latency saves): the line is at 400 000 cells.  One FP32
-// mesh takes them up to 650 000: 660^2 12.4-15.0 / 18.9, 700^2 14.7-15.8 / 19.3
-// (17.0 / 24.4 while four lines grow), 780^2 16.4-17.1 / 19.1, 860^2 18.0-20.3 /
-// 21.7, 960^2 23.2-25.3 / 21.8.
+// mesh takes them up to 650 000: 400^2 10.3 / 19.3 [10.5 / 20.0], 600^2 11.4 /
+// 18.6 [13.0 / 19.9], 700^2 13.4 / 19.1 [14.9 / 20.0], 800^2 17.6 / 19.6 [20.0 /
+// 21.1], 860^2 18.5-20 / 18.6.  20 FP64 members of 64 to 200 a side: 52 / 56; in
+// their first steps, with every line growing, the step kernel takes 37 either way.
 //
 // The tile is of whole atmosphere cells, at least 8 cells a side, and never
 // larger than the largest member.  FP64 (84 vector registers: 20 waves on a

@@ -12,9 +12,12 @@
 // Bound by latency: one round trip to memory, then four phases of one node
 // each (FP64: two pow calls) between barriers.  A domain's ignition geometry
 // comes in the kernel's arguments, formed on the host, so the step is one
-// launch.  128^2 FP64 (169 work-groups of 10 x 10 cells) 35 -> 9.3 us per
-// step, FP32 17 -> 7.6; 512^2 FP64 36 -> 23, FP32 17 -> 11; 517 x 389 FP32
-// with four lines being lit 23 -> 12.
+// launch.  128^2 FP64 (169 work-groups of 10 x 10 cells) 37 -> 10.5 us per
+// step, 500^2 FP64 33.6 -> 23.3, FP32 15.3 -> 10.8; 500^2 FP32 while four lines
+// grow 19.7 -> 12.0.  Every active ignition is evaluated at every node: while
+// lines grow, psi_g is below psi at nearly all of them, and dropping the others
+// per wave by bounds over the frame made such steps slower (500^2 FP64 27.9 ->
+// 29.7, 600^2 33.2 -> 36.3: the bounds are a chain before the first barrier).
 #include "fire_device.h"
 
 namespace fire {

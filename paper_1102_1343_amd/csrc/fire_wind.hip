@@ -10,8 +10,8 @@
 //    and the level values above z0 (0 if z_f <= z0, the top value above the
 //    highest level).  Computed in double (float logarithms for float
 //    arrays, see ln_z).
-// 2. k_wind_bilinear, 8 fire rows per work-group: bilinear interpolation
-//    of each component from its staggered points, coordinates clamped to
+// 2. k_wind_bilinear, 3 fire rows of one component per work-group: bilinear
+//    interpolation of the component from its staggered points, coordinates clamped to
 //    the points' extent, in the array precision -- first in y, once per
 //    point of the row's span (into LDS), then in x per fire cell.  The kernel
 //    writes 2 values per fire cell and reads fields ~sr_x sr_y times smaller,
@@ -163,15 +163,18 @@ template <typename T> __device__ __forceinline__ Axis<T> axis(int N, int Dn, T r
 // centre is at x/DX = (i + 1/2)/sr_x; u-points at (I, J + 1/2), v-points at
 // (I + 1/2, J) in atmosphere-cell units.  Arithmetic in the array precision.
 //
-// Bound by the stores of the two outputs.  With both components in one
-// work-group of 8 rows and 32 bytes of a lane in FP64, the two streams met in
-// the same memory channels where a row is a power of two, and FP64 stores left
-// half lines; call times, before -> now: 8192^2 FP32 115.3 -> 98 us (5.5 TB/s
-// of output), FP64 518 -> 224 us; 4000^2 FP32 51.6 -> 50.0 us, FP64 90.5 -> 52.4
-// us; 397x301 FP64 15.0 -> 7.6 us (the chain of a work-group's rows).  Rows of
-// a work-group at 8192^2 FP32: 1: 158 us (the x positions are then formed for
-// every row), 2: 111, 3: 98, 4: 109, 6: 114: bands of an odd number of rows keep
-// work-groups at work together off each other's channels.
+// Bound by the stores of the two outputs.  Both components in one work-group
+// of 8 rows, with 32 bytes of a lane in FP64 (FP64 stores then left half
+// lines), before -> now, us a call back to back: 8192^2 FP32 121.7 -> 103.6
+// (98 of them in this kernel: 5.5 TB/s of output), 4000^2 FP32 38.9 -> 32.4,
+// FP64 124.1 -> 61.0, 4096^2 FP64 132.2 -> 63.5, 5001^2 FP32 (no vector stores)
+// 85.2 -> 81.1.  At 397x301 FP64 the kernels take 7.6 us instead of 15.0, but
+// the call is the caller's host work (18 us before and now).  Rows of a
+// work-group, 2 / 3 / 4 / 6 / 8: 8192^2 FP32 122 / 104 / 106 / 120 / 121, 4000^2
+// 37.1 / 32.4 / 31.8 / 35.6 / 36.3, 600^2 at refinement 1 22.9 / 22.2 / 23.6 /
+// 23.8 / 24.6, 4000^2 FP64 58.7 / 61.0 / 63.3 / 64.4 / 65.5 (1 row: 158 at 8192^2,
+// the x positions are then formed for every row): 3 is within 4 % of the best
+// at every size and type, powers of two and others alike.
 constexpr int kWChunk = 4 * kWB;
 constexpr int kWRows = 3;
 // staggered points a chunk can span: (kWChunk - 1)/sr_x + 3 at most

@@ -1,5 +1,5 @@
-"""The small-tile step (meshes up to 400 000 cells with no tile shape set)
-against the tiled one: the same functions at every node, so psi, t_i, F, both
+"""The small-tile step (meshes up to 400 000 cells, or 650 000 of one
+single-precision mesh, with no tile shape set) against the tiled one: the same functions at every node, so psi, t_i, F, both
 fluxes and the status are equal bit for bit."""
 from __future__ import annotations
 
@@ -44,7 +44,8 @@ def _run(prob, dtype, tile):
 
 # (nx, ny, sr_x, sr_y, tile of the tiled run): two nodes, one cell past a tile,
 # ragged, one cell per atmosphere cell, cells wider than a wave, long and
-# narrow, two nodes per thread, the last size of the small tiles and the next
+# narrow, two nodes per thread, the last double-precision size of the small
+# tiles and the next
 CASES = [(2, 2, 10, 10, (10, 10)), (3, 40, 1, 1, (60, 20)), (11, 10, 10, 10, (120, 20)),
          (20, 21, 10, 10, (60, 10)), (97, 63, 8, 5, (120, 20)), (130, 29, 61, 26, (122, 26)),
          (700, 9, 4, 3, (120, 18)), (9, 700, 4, 3, (120, 18)), (331, 257, 10, 10, (120, 20)),
