@@ -183,17 +183,17 @@ step_tile(const StepArgs &a, const int tile, const int tx, const int tyv, const 
           const T *__restrict__ irow) {
     // A wave's 64 lanes share one frame row: in a scalar register, the row's
     // range tests and LDS row offsets cost no vector work, which is what the
-    // plain step is short of where it fills the chip (84 % of the cycles of an
-    // unburnt 8192^2 step), but they lengthen the chain of a wave, which is the
-    // time where it does not, and of the ensembles (step_rows() has the rule).
-    // Each
-    // phase forms them, and the masks of the lanes' columns, from copies of
-    // its own: shared between the phases, they do not fit the scalar registers
-    // of 8 waves per SIMD (30 spills in the FP32 120 x 20 kernel, two to four
-    // reloads from vector lanes in every row of the edge tiles' passes and of
-    // stage 2; with the copies 9, outside the row loops, 63 vector registers).
-    // Per step, vector row -> scalar row -> copies: 8192^2 556 -> 520 -> 517 us,
-    // 4099x4001 with fires 181 -> 179 -> 176 us, 2048^2 41.4 -> 39.2 -> 37.8 us.
+    // plain step is short of where it fills the chip (80 % of the cycles of the
+    // first 330 steps at 8192^2, 85 % with 40 % burning), but they lengthen the
+    // chain of a wave, which is the time where it does not, and of the
+    // ensembles (step_rows() has the rule).  Each phase forms them, and the
+    // masks of the lanes' columns, from copies of its own: shared between the
+    // phases, they do not fit the scalar registers of 8 waves per SIMD (30
+    // spills in the FP32 120 x 20 kernel, two to four reloads from vector lanes
+    // in every row of the edge tiles' passes and of stage 2; with the copies 9,
+    // outside the row loops, 63 vector registers).  Per step, vector row ->
+    // scalar row -> copies: 8192^2 556 -> 520 -> 517 us, 4099x4001 with fires 181
+    // -> 179 -> 176 us, 2048^2 41.4 -> 39.2 -> 37.8 us.
     const int ty = SROW ? __builtin_amdgcn_readfirstlane(tyv) : tyv;
     auto row_copy = [](int v) { return SROW ? phase_copy(v) : lane_copy(v); };
     constexpr int FHM = kNR * KR;

@@ -1,6 +1,7 @@
 """The small-tile step (meshes up to 400 000 cells, or 650 000 of one
-single-precision mesh, with no tile shape set) against the tiled one: the same functions at every node, so psi, t_i, F, both
-fluxes and the status are equal bit for bit."""
+single-precision mesh, with no tile shape set) against the tiled one: the same
+functions at every node, so psi, t_i, F, both fluxes and the status are equal
+bit for bit."""
 from __future__ import annotations
 
 import math
