@@ -95,7 +95,8 @@ void ignition_window(const fire_ignition *ign, int n, double *lo, double *hi) {
 // cost more than the latency saves): the line is at 400 000 cells.  One FP32
 // mesh takes them up to 650 000: 400^2 10.3 / 19.3 [10.5 / 20.0], 600^2 11.4 /
 // 18.6 [13.0 / 19.9], 700^2 13.4 / 19.1 [14.9 / 20.0], 800^2 17.6 / 19.6 [20.0 /
-// 21.1], 860^2 18.5-20 / 18.6.  20 FP64 members of 64 to 200 a side: 52 / 56; in
+// 21.1], 860^2 18.5-20 / 18.6.  FP32 ensembles stay at 400 000 (8 steps, us: 60
+// members of 64 to 110 a side 316 / 302, 4 of 300 to 420 311 / 284).  20 FP64 members of 64 to 200 a side: 52 / 56; in
 // their first steps, with every line growing, the step kernel takes 37 either way.
 //
 // The tile is of whole atmosphere cells, at least 8 cells a side, and never
