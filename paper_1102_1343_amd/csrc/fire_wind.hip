@@ -35,7 +35,6 @@ constexpr int kWB = 256;
 
 struct WindArgs {
     int32_t nax, nay, nz, sr_x, sr_y, nx, ny;
-    int32_t vec;       // every row of both outputs starts on 16 bytes: vector stores
     double zf, g;
     int32_t nchunk;    // kWChunk-cell chunks of a fire row
     double lzf;        // ln z_f
@@ -159,7 +158,9 @@ template <typename T> __device__ __forceinline__ Axis<T> axis(int N, int Dn, T r
 // then interpolates its 4 cells in x from that line, with the x positions and
 // weights formed once for all the rows.  When rows start on 16 bytes, a store
 // is 16 bytes of each lane, non-temporal, 1 KiB in a row of a wave: 4 cells in
-// FP32, 2 in FP64 (the FP64 lane's other two lie half a chunk on).  A fire
+// FP32, 2 in FP64 (the FP64 lane's other two lie half a chunk on); else a lane's
+// cells lie a quarter of a chunk apart, so that a store of a wave fills whole
+// lines.  A fire
 // centre is at x/DX = (i + 1/2)/sr_x; u-points at (I, J + 1/2), v-points at
 // (I + 1/2, J) in atmosphere-cell units.  Arithmetic in the array precision.
 //
@@ -167,8 +168,10 @@ template <typename T> __device__ __forceinline__ Axis<T> axis(int N, int Dn, T r
 // of 8 rows, with 32 bytes of a lane in FP64 (FP64 stores then left half
 // lines), before -> now, us a call back to back: 8192^2 FP32 121.7 -> 103.6
 // (98 of them in this kernel: 5.5 TB/s of output), 4000^2 FP32 38.9 -> 32.4,
-// FP64 124.1 -> 61.0, 4096^2 FP64 132.2 -> 63.5, 5001^2 FP32 (no vector stores)
-// 85.2 -> 81.1.  At 397x301 FP64 the kernels take 7.6 us instead of 15.0, but
+// FP64 124.1 -> 61.0, 4096^2 FP64 132.2 -> 63.5.  Without vector stores, start /
+// with 4 cells in a row in each lane / now: 5001^2 FP32 79.3 / 74.7 / 52.8,
+// 1298x5803 FP32 (a second chunk of 274 cells) 32.0 / 38.4 / 24.8, 4001^2 FP64
+// 92.5 / 64.7 / 64.7.  At 397x301 FP64 the kernels take 7.6 us instead of 15.0, but
 // the call is the caller's host work (18 us before and now).  Rows of a
 // work-group, 2 / 3 / 4 / 6 / 8: 8192^2 FP32 122 / 104 / 106 / 120 / 121, 4000^2
 // 37.1 / 32.4 / 31.8 / 35.6 / 36.3, 600^2 at refinement 1 22.9 / 22.2 / 23.6 /
@@ -184,9 +187,10 @@ constexpr int kWLine = kWChunk + 4;
 template <typename T> constexpr int kWVec = 16 / (int)sizeof(T);
 template <typename T> using WV = T __attribute__((ext_vector_type(kWVec<T>)));
 
+// VEC: every row of both outputs starts on 16 bytes.
 // One component of the work-group's rows: nk x nl staggered points pf, fire
 // centre i at (2i + 1 - sx) / (2 sr_x) in them, row j at (2j + 1 - sy) / (2 sr_y).
-template <typename T>
+template <typename T, bool VEC>
 __device__ __forceinline__ void wind_rows(const WindArgs &a, const T *pf, T *out, int nk, int nl,
                                           int sx, int sy, int j0, int c0, T (*L)[kWLine]) {
     const int Dx = 2 * a.sr_x, Dy = 2 * a.sr_y;
@@ -197,18 +201,20 @@ __device__ __forceinline__ void wind_rows(const WindArgs &a, const T *pf, T *out
     const int pe = axis(2 * c1 + 1 - sx, Dx, rx, nk).k1;
     // this thread's cells: line positions and weights, the same in every row
     constexpr int V = kWVec<T>, G = 4 / V;
-    const int i0 = c0 + V * threadIdx.x;
+    auto cell = [&](int q) {
+        return VEC ? c0 + V * (int)threadIdx.x + (q / V) * (V * kWB) + q % V
+                   : c0 + (int)threadIdx.x + q * kWB;
+    };
     int k0[4], k1[4];
     T t[4];
 #pragma unroll
     for (int q = 0; q < 4; q++) {
-        const int c = i0 + (q / V) * (V * kWB) + q % V;
+        const int c = cell(q);
         const Axis<T> x = axis(2 * (c < a.nx ? c : a.nx - 1) + 1 - sx, Dx, rx, nk);
         k0[q] = x.k0 - pb;
         k1[q] = x.k1 - pb;
         t[q] = x.t;
     }
-    const bool vec = a.vec != 0;
     const int j1 = j0 + kWRows < a.ny ? j0 + kWRows : a.ny;
     int p = 0;
     for (int j = j0; j < j1; j++, p ^= 1) {
@@ -220,28 +226,26 @@ __device__ __forceinline__ void wind_rows(const WindArgs &a, const T *pf, T *out
             L[p][q] = (T(1) - y.t) * p0[pb + q] + y.t * p1[pb + q];
         __syncthreads();
         T *row = out + (size_t)j * a.nx;
+        auto value = [&](int q) { return (T(1) - t[q]) * L[p][k0[q]] + t[q] * L[p][k1[q]]; };
+        if (VEC) {   // streaming (non-temporal) stores: the output is not re-read here
 #pragma unroll
-        for (int g = 0; g < G; g++) {
-            const int c = i0 + g * (V * kWB);
-            if (c < a.nx) {
+            for (int g = 0; g < G; g++) {
+                const int c = cell(g * V);
+                if (c >= a.nx) continue;
                 WV<T> o;
 #pragma unroll
-                for (int q = 0; q < V; q++) {
-                    const int r = g * V + q;
-                    o[q] = (T(1) - t[r]) * L[p][k0[r]] + t[r] * L[p][k1[r]];
-                }
-                if (vec)   // streaming (non-temporal) stores: the output is not re-read here
-                    __builtin_nontemporal_store(o, reinterpret_cast<WV<T> *>(row + c));
-                else
-#pragma unroll
-                    for (int q = 0; q < V; q++)
-                        if (c + q < a.nx) row[c + q] = o[q];
+                for (int q = 0; q < V; q++) o[q] = value(g * V + q);
+                __builtin_nontemporal_store(o, reinterpret_cast<WV<T> *>(row + c));
             }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                if (cell(q) < a.nx) row[cell(q)] = value(q);
         }
     }
 }
 
-template <typename T>
+template <typename T, bool VEC>
 __global__ void __launch_bounds__(kWB)
 k_wind_bilinear(const WindArgs a, const T *uf, const T *vf, T *u, T *v) {
     __shared__ T L[2][kWLine];
@@ -251,9 +255,9 @@ k_wind_bilinear(const WindArgs a, const T *uf, const T *vf, T *u, T *v) {
     const int j0 = band * kWRows;
     const int c0 = (blockIdx.x - band * a.nchunk) * kWChunk;
     if (blockIdx.z == 0)
-        wind_rows(a, uf, u, a.nax + 1, a.nay, 0, a.sr_y, j0, c0, L);
+        wind_rows<T, VEC>(a, uf, u, a.nax + 1, a.nay, 0, a.sr_y, j0, c0, L);
     else
-        wind_rows(a, vf, v, a.nax, a.nay + 1, a.sr_x, 0, j0, c0, L);
+        wind_rows<T, VEC>(a, vf, v, a.nax, a.nay + 1, a.sr_x, 0, j0, c0, L);
 }
 
 bool grid_ok(const fire_wind_grid *g) {
@@ -286,7 +290,8 @@ hipError_t run(const fire_wind_grid *g, const void *u3, const void *v3, const vo
     a.sr_y = g->sr_y;
     a.nx = g->nx;
     a.ny = g->ny;
-    a.vec = (g->nx % kWVec<T> == 0) && ((uintptr_t)u % 16 == 0) && ((uintptr_t)v % 16 == 0);
+    // every row of both outputs starts on 16 bytes: vector stores
+    const bool vec = (g->nx % kWVec<T> == 0) && ((uintptr_t)u % 16 == 0) && ((uintptr_t)v % 16 == 0);
     a.zf = g->zf;
     a.g = g->g;
     a.nchunk = (g->nx + kWChunk - 1) / kWChunk;
@@ -299,7 +304,8 @@ hipError_t run(const fire_wind_grid *g, const void *u3, const void *v3, const vo
     hipLaunchKernelGGL(k_wind_vertical<T>, dim3((npts + kWB - 1) / kWB), dim3(kWB), 0, s, a,
                        (const T *)u3, (const T *)v3, (const T *)phi, (const T *)hgt,
                        (const T *)z0, uf, vf);
-    hipLaunchKernelGGL(k_wind_bilinear<T>,
+    auto *fn = vec ? k_wind_bilinear<T, true> : k_wind_bilinear<T, false>;
+    hipLaunchKernelGGL(fn,
                        dim3((unsigned)((g->ny + kWRows - 1) / kWRows) * (unsigned)a.nchunk, 1, 2),
                        dim3(kWB), 0, s, a, (const T *)uf, (const T *)vf, (T *)u, (T *)v);
     return hipGetLastError();

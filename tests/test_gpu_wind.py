@@ -122,3 +122,18 @@ def test_outputs_at_any_element_get_the_same_values(dt, nx, ny):
         for w, o, f in zip(want, out, flat):
             assert torch.equal(o, w), (nx, ny, off)
             assert (f[:off] == -77.0).all() and (f[off + n:] == -77.0).all()
+
+
+@pytest.mark.parametrize("dt", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("sr", [1, 10])
+def test_rows_of_any_length_get_the_same_values(dt, sr):
+    """A cell's wind does not depend on where its row ends: rows that end at,
+    before and past each quarter of a 1024-cell chunk against whole chunks."""
+    nax, nay, ny = -(-2052 // sr), 3, min(3 * sr, 7)
+    atm = synth.atmosphere(nax, nay, nz=3, dx=24.0, dy=24.0, seed=7)
+    args = [_dev(atm[k], dt) for k in ("u3", "v3", "phi", "hgt", "z0")]
+    want = F.wind_interp(*args, 2048, ny, sr, sr)
+    for nx in (1, 63, 255, 257, 511, 513, 767, 769, 1023, 1025, 1279, 1281, 1298, 2047):
+        got = F.wind_interp(*args, nx, ny, sr, sr)
+        for w, g in zip(want, got):
+            assert torch.equal(g, w[:, :nx]), nx
